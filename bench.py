@@ -283,7 +283,8 @@ def main():
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "eval_kernel_cost_adjoint_32x32x8_traffic.txt")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2310_17274_amd", "csrc", f)
-                  for f in ("mg_eval.h", "mg_eval_wl.h", "mg_device.h", "mg_internal.h", "mg_solver.h")]
+                  for f in ("mg_eval.h", "mg_eval_lane.h", "mg_eval_wl.h", "mg_device.h", "mg_internal.h",
+                            "mg_solver.h")]
 
 
 def kernel_digest():

@@ -245,8 +245,8 @@ mg_status mg_set_self_collision(mg_ctx *ctx, int n_pairs, const int *pairs);
 mg_status mg_ee_pose(mg_ctx *ctx, int rows, const float *q, float *pose, void *stream);
 
 /* Evaluation layouts.  Lane per link (layout 0): 8 or 16 lanes per
- * evaluation, one per link, with the world's cuboids split over 1, 2 or 4
- * waves ("slices").  Wave per link (layout 1): 64 evaluations per
+ * evaluation, one per link, times 1, 2 or 4 copies ("slices") that share the
+ * work on its cuboids.  Wave per link (layout 1): 64 evaluations per
  * workgroup, one wave per link plus one for the joint terms, each wave
  * skipping the cuboids that a ball around its link's spheres over all 64
  * lanes cannot reach (with swept collision, the ball grows by half the
@@ -276,8 +276,7 @@ mg_status mg_ee_pose(mg_ctx *ctx, int rows, const float *q, float *pose, void *s
  * be NULL) receives the slice count for the lane-per-link layout, minus
  * the workgroups per 64 evaluations for the wave-per-link layout, -8 for
  * two waves per link, -16 for two slot groups per wave or -32 for four.
- * Overwrites the batch's evaluation workspaces; not capturable.  With
- * swept collision the lane-per-link layout takes one slice. */
+ * Overwrites the batch's evaluation workspaces; not capturable. */
 mg_status mg_batch_set_layout(mg_batch *batch, int layout, int slices);
 
 /* Choice folded into the next evaluation (Alg.1 and Alg.6 inside the

@@ -67,9 +67,12 @@ void dev_free(T*& p) {
   p = nullptr;
 }
 
-// Cuboid slices per evaluation group offered by the evaluation kernel.
-constexpr int kNumSlices = 3;
-constexpr int kSlices[kNumSlices] = {1, 2, 4};
+// Lane-per-link copies of an evaluation that split its cuboids (robots of
+// up to 8 links: all four; longer ones the first three), and rows per
+// workgroup (a power of two up to the evaluations of a workgroup).
+constexpr int kNumSlices = 4;
+constexpr int kSlices[kNumSlices] = {1, 2, 4, 8};
+constexpr int kNumRowBlocks = 6;   // 1, 2, .. 32 rows
 
 }  // namespace
 
@@ -77,6 +80,7 @@ struct mg_ctx {
   int device = 0;
   int L = 0, D = 0, M = 0, n_ee = 0;
   int lpe = 8, maxs = 4;     // lanes per evaluation, sphere slots per link
+  int max_spheres = 0;       // most spheres on any link
   std::vector<int> parent, joint, sphere_link, ee_link;
   std::vector<float> fixed_tf, sphere, ee_tf, q_lo, q_hi;
   mg::Params params{};
@@ -115,10 +119,12 @@ struct mg_batch {
   mg_ctx* ctx = nullptr;
   int P = 0, n_seeds = 0, rows = 0, K_max = 0, m_max = 0;
   std::vector<int> seeds, horizon, world;
+  std::vector<mg::Problem> prob;
   mg::Problem* d_prob = nullptr;
   mg::SeedInfo* d_seed = nullptr;
-  int* d_chunk[kNumSlices] = {nullptr, nullptr, nullptr};
-  int chunks[kNumSlices] = {0, 0, 0};
+  int* d_chunk[kNumRowBlocks] = {};   // workgroups of 1 << i rows before each problem
+  int chunks[kNumRowBlocks] = {};
+  int uni_rows = 0;   // rows of every problem when they all have the same number, else 0
   int max_n = 0;      // largest T*D of a seed
   int uniform_T = 0;  // the horizon when every problem has the same one, else 0
   float *cost_e = nullptr, *gd_e = nullptr, *mc_e = nullptr, *grad_e = nullptr, *pe_e = nullptr;
@@ -142,7 +148,8 @@ struct mg_batch {
   bool timing = false;
   std::vector<hipEvent_t> ev_start, ev_stop;
   int ev_next = 0, ev_count = 0;
-  int slices = -1;    // forced cuboid slices index (-1: automatic)
+  int slices = -1;    // cuboid slices index (-1: automatic)
+  long tuned_evals = 0;   // evaluations of the launch the autotuner chose `slices` for
   int layout = -1;    // evaluation layout: -1 automatic, 0 lane per link, 1 wave per link
   bool layout_set = false;   // the layout came from mg_batch_set_layout (not the autotuner)
   // wave-per-link chunks of 64 evaluations, per candidate count K
@@ -191,10 +198,11 @@ mg_status build_lanes(mg_ctx* c) {
   int most = 0;
   for (int l = 0; l < c->L; ++l) most = std::max(most, count[l]);
   c->maxs = most <= 4 ? 4 : most <= 8 ? 8 : 16;
+  c->max_spheres = most;
   if (most > 16) return fail(MG_ERR_UNSUPPORTED, "a link carries %d spheres (at most 16)", most);
   const int lpe = c->lpe, maxs = c->maxs;
   std::vector<int4> info(lpe);
-  std::vector<float4> sph((size_t)lpe * maxs, make_float4(0.0f, 0.0f, 0.0f, 0.0f));
+  std::vector<float4> sph((size_t)lpe * maxs, make_float4(0.0f, 0.0f, 0.0f, -1e30f));
   std::vector<int> fill(lpe, 0);
   for (int l = 0; l < lpe; ++l) {
     if (l >= c->L) { info[l] = make_int4(l, l + 1, 0, -1); continue; }
@@ -297,6 +305,8 @@ mg::Lanes dev_lanes(const mg_ctx* c) {
   mg::Lanes ln;
   ln.lpe = c->lpe;
   ln.maxs = c->maxs;
+  ln.used = c->max_spheres;
+  ln.kb = ln.rb = ln.uni_rows = 0;
   ln.info = c->d_lane_info;
   ln.sphere = c->d_lane_sphere;
   return ln;
@@ -305,7 +315,6 @@ mg::Lanes dev_lanes(const mg_ctx* c) {
 mg::WaveLinks dev_wave_links(const mg_ctx* c) {
   mg::WaveLinks wl{};
   wl.info = c->d_wl_info;
-  wl.chain = c->d_wl_chain;
   wl.sphere = c->d_lane_sphere;
   wl.ball = c->d_wl_ball;
   wl.maxs = c->maxs;
@@ -358,10 +367,21 @@ bool use_wl(const mg_batch* b, int K) {
   const mg_ctx* c = b->ctx;
   if (!wl_possible(c) || K > b->K_max) return false;
   if (needs_wl(c)) return true;     // self-collision and the speed metric live in this layout only
-  if (b->layout >= 0) return b->layout == 1;
+  // (the autotuner's layout holds for the candidate count it timed)
+  if (b->layout >= 0 && (b->layout_set || (long)b->rows * K == b->tuned_evals)) return b->layout == 1;
   const char* env = getenv("MG_EVAL_LAYOUT");
   if (env) return atoi(env) == 1;
   return false;
+}
+
+// The reciprocals of the joint terms, for the parameters' current dt and
+// eta2.
+void set_reciprocals(mg::Params& d) {
+  const float h = d.dt;
+  d.inv_e2 = 1.0f / d.eta2;
+  d.cv = 1.0f / (12.0f * h);
+  d.ca = 1.0f / (12.0f * h * h);
+  d.cj = 1.0f / (2.0f * h * h * h);
 }
 
 mg::Params to_dev(const mg_params& p) {
@@ -373,6 +393,7 @@ mg::Params to_dev(const mg_params& p) {
   d.ls_eta1 = p.ls_eta1; d.ls_eta_w = p.ls_eta_w;
   d.success_pos = p.success_pos; d.success_rot = p.success_rot;
   d.w_self = p.w_self; d.n_self = 0; d.speed = p.speed;
+  set_reciprocals(d);
   return d;
 }
 
@@ -386,23 +407,57 @@ mg_status check_params(const mg_params* p) {
   return MG_OK;
 }
 
-// Cuboid slices for a call evaluating n_evals rows x candidates: the fewest
-// slices (least repeated kinematics) that still give every SIMD about four
-// wavefronts; MG_CUBOID_SLICES forces a choice.
+// Lane-per-link copies (an index into kSlices) for a call evaluating n_evals
+// rows x candidates: the fewest (least repeated kinematics) that still give
+// every SIMD about kLplTarget wavefronts; MG_CUBOID_SLICES forces a choice.
+// A choice of the autotuner holds for the number of evaluations it timed.
 int pick_slices(const mg_batch* b, long n_evals) {
-  if (b->ctx->params.swept) return 0;   // the swept kernels take whole worlds
-  if (b->slices >= 0) return b->slices;
+  const int n_opts = b->ctx->lpe == 8 ? kNumSlices : kNumSlices - 1;
+  if (b->slices >= 0 && (b->layout_set || n_evals == b->tuned_evals)) return b->slices;
   const char* env = getenv("MG_CUBOID_SLICES");
   if (env) {
     const int h = atoi(env);
-    for (int i = 0; i < kNumSlices; ++i)
+    for (int i = 0; i < n_opts; ++i)
       if (kSlices[i] == h) return i;
   }
   const long waves1 = (n_evals * b->ctx->lpe + mg::kWave - 1) / mg::kWave;
-  const long target = 256L * 4 * 4;   // CUs x SIMDs x waves
-  for (int i = 0; i < kNumSlices; ++i)
+  const long target = 256L * 4;   // CUs x SIMDs
+  for (int i = 0; i < n_opts; ++i)
     if (waves1 * kSlices[i] >= target) return i;
-  return kNumSlices - 1;
+  return n_opts - 1;
+}
+
+// Lane-per-link workgroup of a launch with K candidates per row: as many
+// candidates side by side as divide K (they sit close together in
+// configuration space and share their staged rows), the rest of the
+// workgroup's evaluations are rows.  Returns the workgroups along x.
+int lane_blocks(const mg_batch* b, int hi, int K, mg::EvalArgs& a) {
+  const int epb = mg::kBlock / (b->ctx->lpe * kSlices[hi]);
+  int kb = 1;
+  while (kb * 2 <= epb && K % (kb * 2) == 0) kb *= 2;
+  int ri = 0;
+  while ((1 << ri) < epb / kb) ++ri;
+  a.slices = kSlices[hi];
+  a.ln.kb = kb;
+  a.ln.rb = epb / kb;
+  a.ln.uni_rows = b->uni_rows;
+  a.chunk_prefix = b->d_chunk[ri];
+  return b->chunks[ri];
+}
+
+// One problem: the wave-per-link kernel forms its chunk records from the
+// workgroup index (the same records the table holds).
+void wl_single(const mg_batch* b, int K, mg::WaveLinks& wl) {
+  wl.one.S = 0;
+  if (b->P != 1) return;
+  const mg_ctx* c = b->ctx;
+  const int w = b->world[0];
+  const bool set = w + 1 < (int)c->world_off.size();
+  wl.one.S = b->seeds[0];
+  wl.one.T = b->horizon[0];
+  wl.one.box_lo = set ? c->world_off[w] : 0;
+  wl.one.box_hi = set ? c->world_off[w + 1] : 0;
+  wl.one.n_e = b->seeds[0] * b->horizon[0] * K;
 }
 
 mg::EvalArgs eval_args(const mg_ctx* c, const mg_batch* b, int hi, const float* q_start,
@@ -414,13 +469,12 @@ mg::EvalArgs eval_args(const mg_ctx* c, const mg_batch* b, int hi, const float* 
   a.wl = dev_wave_links(c);
   a.pr = c->params;
   a.pr.n_self = c->n_self;
-  a.slices = kSlices[hi];
   a.prob = b->d_prob;
-  a.chunk_prefix = b->d_chunk[hi];
+  lane_blocks(b, hi, K, a);
+  wl_single(b, K, a.wl);
   a.P = b->P;
   a.rows = b->rows;
   a.box = c->d_box;
-  a.world_off = c->d_world_off;
   a.q_start = q_start;
   a.goal = goal;
   a.x = x;
@@ -474,6 +528,15 @@ mg_status wl_records(mg_batch* b, int K, int E, mg::WlChunk** dptr, int* count) 
 // particle stage's records when particles are reserved.
 mg_status wl_chunks_upload(mg_batch* b) {
   mg_status st;
+  // the problems' records carry their worlds' cuboid ranges too
+  const mg_ctx* c = b->ctx;
+  for (int p = 0; p < b->P; ++p) {
+    const int w = b->world[p];
+    const bool set = w + 1 < (int)c->world_off.size();
+    b->prob[p].box_lo = set ? c->world_off[w] : 0;
+    b->prob[p].box_hi = set ? c->world_off[w + 1] : 0;
+  }
+  HIP_TRY(hipMemcpy(b->d_prob, b->prob.data(), b->prob.size() * sizeof(mg::Problem), hipMemcpyHostToDevice));
   for (int K = 1; K <= b->K_max; ++K)
     for (int gi = 0; gi < 3; ++gi)
       if ((st = wl_records(b, K, mg::kWave >> gi, &b->d_chunk_wl[K][gi], &b->chunks_wl[K][gi])) != MG_OK)
@@ -499,21 +562,6 @@ mg_status common_checks(mg_ctx* c, mg_batch* b) {
 // index hi) or wave per link.
 // Wave-per-link slices: the forced count, else enough workgroups for two
 // per CU.
-// One problem: the wave-per-link kernel forms its chunk records from the
-// workgroup index (the same records the table holds).
-void wl_single(const mg_batch* b, int K, mg::WaveLinks& wl) {
-  wl.one.S = 0;
-  if (b->P != 1) return;
-  const mg_ctx* c = b->ctx;
-  const int w = b->world[0];
-  const bool set = w + 1 < (int)c->world_off.size();
-  wl.one.S = b->seeds[0];
-  wl.one.T = b->horizon[0];
-  wl.one.box_lo = set ? c->world_off[w] : 0;
-  wl.one.box_hi = set ? c->world_off[w + 1] : 0;
-  wl.one.n_e = b->seeds[0] * b->horizon[0] * K;
-}
-
 int wl_slices(const mg_batch* b, int K) {
   if (b->wl_slices > 0) return std::min(b->wl_slices, b->wl_slices_max);
   int h = 1;
@@ -536,13 +584,12 @@ hipError_t launch_layout(mg_batch* b, mg::EvalArgs a, int hi, bool cand, bool gr
     a.wl.halves = halves;
     a.wl.groups = groups;
     a.wl.chunk = b->d_chunk_wl[a.K][groups_index(groups)];
-    wl_single(b, a.K, a.wl);
     // (the speed's gradient terms need every cuboid of a sphere in one workgroup)
     const int wls = (halves == 2 || groups > 1 || !slices_ok || (a.sp_h && grad)) ? 1 : wl_slices(b, a.K);
     return mg::launch_eval_wl(a, b->chunks_wl[a.K][groups_index(groups)], wls, cand, grad, s, fs);
   }
   if (fs) return hipErrorInvalidValue;
-  return mg::launch_eval(a, b->chunks[hi], cand, grad, s);
+  return mg::launch_eval(a, lane_blocks(b, hi, a.K, a), cand, grad, s);
 }
 
 // Per-(candidate, row) outputs of an evaluation launch held outside the
@@ -926,28 +973,28 @@ mg_status mg_batch_create(mg_ctx* c, int P, const int* seeds, const int* horizon
   b->uniform_T = horizon[0];
   for (int p = 1; p < P; ++p)
     if (horizon[p] != horizon[0]) b->uniform_T = 0;
-  std::vector<mg::Problem> prob(P);
+  b->uni_rows = seeds[0] * horizon[0];
+  for (int p = 1; p < P; ++p)
+    if (seeds[p] * horizon[p] != b->uni_rows) b->uni_rows = 0;
   std::vector<mg::SeedInfo> sinfo;
   sinfo.reserve(n_seeds);
   int r0 = 0, s0 = 0;
   for (int p = 0; p < P; ++p) {
     b->max_n = std::max(b->max_n, horizon[p] * c->D);
-    prob[p] = mg::Problem{seeds[p], horizon[p], world[p], r0, s0, 0, 0, 0};
+    b->prob.push_back(mg::Problem{seeds[p], horizon[p], world[p], r0, s0, 0, 0, 0});
     for (int s = 0; s < seeds[p]; ++s) sinfo.push_back(mg::SeedInfo{r0 + s * horizon[p], horizon[p], p, 0});
     r0 += seeds[p] * horizon[p];
     s0 += seeds[p];
   }
   mg_status st;
   auto bail = [&](mg_status s) { mg_batch_destroy(b); return s; };
-  if ((st = dev_upload(&b->d_prob, prob)) != MG_OK) return bail(st);
+  if ((st = dev_alloc(&b->d_prob, (size_t)P)) != MG_OK) return bail(st);
   if ((st = dev_upload(&b->d_seed, sinfo)) != MG_OK) return bail(st);
-  for (int hi = 0; hi < kNumSlices; ++hi) {
-    // evaluations per workgroup: (waves / slices) groups of (wave / lanes) rows
-    const int epb = (mg::kBlock / mg::kWave / kSlices[hi]) * (mg::kWave / c->lpe);
+  for (int ri = 0; ri < kNumRowBlocks; ++ri) {
     std::vector<int> pre(P + 1, 0);
-    for (int p = 0; p < P; ++p) pre[p + 1] = pre[p] + (seeds[p] * horizon[p] + epb - 1) / epb;
-    b->chunks[hi] = pre[P];
-    if ((st = dev_upload(&b->d_chunk[hi], pre)) != MG_OK) return bail(st);
+    for (int p = 0; p < P; ++p) pre[p + 1] = pre[p] + (seeds[p] * horizon[p] + (1 << ri) - 1) / (1 << ri);
+    b->chunks[ri] = pre[P];
+    if ((st = dev_upload(&b->d_chunk[ri], pre)) != MG_OK) return bail(st);
   }
   c->batches.push_back(b);
   if ((st = wl_chunks_upload(b)) != MG_OK) return bail(st);
@@ -1182,7 +1229,7 @@ mg_status mg_autotune(mg_ctx* c, mg_batch* b, const float* q_start, const float*
   struct Opt { int layout, hi, halves, wls, groups; };
   std::vector<Opt> opts;
   if (!needs_wl(c))
-    for (int hi = 0; hi < kNumSlices; ++hi) opts.push_back({0, hi, 0, 0, 1});
+    for (int hi = 0; hi < 3; ++hi) opts.push_back({0, hi, 0, 0, 1});
   if (wl_groups_possible(c, 4)) opts.push_back({1, -1, 1, 1, 4});
   if (wl_groups_possible(c)) opts.push_back({1, -1, 1, 1, 2});
   if (wl_halves_possible(c)) opts.push_back({1, -1, 2, 1, 1});
@@ -1191,6 +1238,8 @@ mg_status mg_autotune(mg_ctx* c, mg_batch* b, const float* q_start, const float*
   if (opts.empty()) return fail(MG_ERR_UNSUPPORTED, "no evaluation layout fits this robot");
   size_t best = 0;
   float best_us = 3.0e38f;
+  b->layout_set = false;
+  b->tuned_evals = (long)b->rows * K;
   for (size_t o = 0; o < opts.size(); ++o) {
     b->layout = opts[o].layout;
     b->slices = opts[o].hi;
@@ -1208,10 +1257,12 @@ mg_status mg_autotune(mg_ctx* c, mg_batch* b, const float* q_start, const float*
       b->wl_groups = 1;
       return st;
     }
+    // a layout in which the solve folds its choice in saves a launch of about
+    // 4 us per iteration (5.2 us and its gap, against 2.5 us folded in)
+    if (opts[o].layout == 1 && fuse_ok(c, b, K, std::min(4, b->m_max), nullptr)) us -= 4.0f;
     if (us < best_us) { best_us = us; best = o; }
   }
   b->layout = opts[best].layout;
-  b->layout_set = false;
   b->slices = opts[best].hi;
   b->wl_halves = opts[best].halves;
   b->wl_slices = opts[best].wls;
@@ -1301,7 +1352,7 @@ mg_status mg_batch_set_layout(mg_batch* b, int layout, int slices) {
   int hi = -1;
   if (slices != 0) {
     for (int i = 0; i < kNumSlices; ++i)
-      if (kSlices[i] == slices) hi = i;
+      if (kSlices[i] == slices && slices <= 4) hi = i;
     // (wave per link also takes 8 and 16 workgroups per chunk)
     const bool wl_ok = layout == 1 && (slices == 8 || slices == 16);
     if (hi < 0 && !wl_ok) return fail(MG_ERR_ARG, "slices must be 0 (automatic), 1, 2 or 4 (wave per link: or 8, 16)");
@@ -1391,11 +1442,10 @@ mg_status particle_rounds(mg_ctx* c, mg_batch* b, const float* q_start, const fl
       a.wl.halves = halves;
       a.wl.groups = groups;
       a.wl.chunk = b->d_chunk_pm[groups_index(groups)];
-      wl_single(b, n_particles, a.wl);
       a.wl.pm_rows = pm_rows;
       HIP_TRY(mg::launch_eval_wl(a, b->chunks_pm[groups_index(groups)], 1, true, false, s));
     } else {
-      HIP_TRY(mg::launch_eval(a, b->chunks[hi], true, false, s));
+      HIP_TRY(mg::launch_eval(a, lane_blocks(b, hi, n_particles, a), true, false, s));
     }
     mg::ParticleArgs pa;
     memset(&pa, 0, sizeof(pa));
@@ -1750,6 +1800,7 @@ mg_status mg_solve_timestep(mg_ctx* c, mg_batch* b, const float* q_start, const 
     const float rho = dt_opt / p0.dt;
     c->params = p0;
     c->params.dt = dt_opt;
+    set_reciprocals(c->params);
     c->params.a7 = p0.a7 * rho;
     const float rho2 = rho * rho, rho3 = rho2 * rho;
     c->params.a8 = p0.a8 * (rho2 * rho2);

@@ -93,14 +93,14 @@ __device__ __forceinline__ float group_min(float v) {
 // (OFF: the range starts OFF bytes into the block, a multiple of 4)
 template <int BYTES, int OFF = 0>
 __device__ __forceinline__ void warm_kernargs() {
-  static_assert(BYTES <= 512, "one load per line, at most 8 lines");
+  static_assert(BYTES <= 576, "one load per line, at most 9 lines");
   static_assert(OFF % 4 == 0, "dword aligned");
   const cint* kp = (const cint*)__builtin_amdgcn_kernarg_segment_ptr() + OFF / 4;
   constexpr int last = (BYTES - 4) / 4;
   const int v0 = kp[0], v1 = kp[16 < last ? 16 : last], v2 = kp[32 < last ? 32 : last];
   const int v3 = kp[48 < last ? 48 : last], v4 = kp[64 < last ? 64 : last], v5 = kp[80 < last ? 80 : last];
-  const int v6 = kp[96 < last ? 96 : last], v7 = kp[112 < last ? 112 : last];
-  asm volatile("" ::"s"(v0), "s"(v1), "s"(v2), "s"(v3), "s"(v4), "s"(v5), "s"(v6), "s"(v7));
+  const int v6 = kp[96 < last ? 96 : last], v7 = kp[112 < last ? 112 : last], v8 = kp[128 < last ? 128 : last];
+  asm volatile("" ::"s"(v0), "s"(v1), "s"(v2), "s"(v3), "s"(v4), "s"(v5), "s"(v6), "s"(v7), "s"(v8));
 }
 
 __device__ __forceinline__ float wave_sum(float v) { return group_sum<kWave>(v); }

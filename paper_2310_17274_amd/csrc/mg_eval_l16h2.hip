@@ -1,0 +1,8 @@
+// Evaluation kernel instantiations: 16 lanes per evaluation, 2 copies splitting the cuboids.
+#include "mg_eval_lane.h"
+
+namespace mg {
+hipError_t launch_eval_l16h2(const EvalArgs& a, int grid_x, bool cand, bool grad, hipStream_t s) {
+  return launch_eval_shape<16, 2>(a, grid_x, cand, grad, s);
+}
+}  // namespace mg

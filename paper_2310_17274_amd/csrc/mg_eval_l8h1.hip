@@ -1,0 +1,8 @@
+// Evaluation kernel instantiations: 8 lanes per evaluation, 1 copy splitting the cuboids.
+#include "mg_eval_lane.h"
+
+namespace mg {
+hipError_t launch_eval_l8h1(const EvalArgs& a, int grid_x, bool cand, bool grad, hipStream_t s) {
+  return launch_eval_shape<8, 1>(a, grid_x, cand, grad, s);
+}
+}  // namespace mg

@@ -1,0 +1,812 @@
+// mg_eval_lane.h -- the evaluation kernel in the lane-per-link layout: cost
+// and adjoint of every (candidate, waypoint row) of a batch in one launch.
+// Instantiated per lane layout in mg_eval_l*.hip so the variants compile in
+// parallel.
+#pragma once
+
+#include "mg_eval.h"
+
+namespace mg {
+namespace {
+
+// Copy of a lane's 3x4 transform from the lane `OFF` below (row_shr) or
+// above (row_shl) within the 16-lane DPP row.
+template <int CTRL>
+__device__ __forceinline__ void dpp12(const float* src, float* dst) {
+#pragma unroll
+  for (int e = 0; e < 12; ++e) dst[e] = dpp<CTRL>(src[e]);
+}
+
+// One Hillis-Steele step of the prefix product along a chain:
+// P <- P(lane - OFF) * P for lanes at least OFF past their chain start.
+template <int OFF>
+__device__ __forceinline__ void scan_step(float* P, bool active) {
+  float Q[12];
+  dpp12<0x110 + OFF>(P, Q);          // row_shr:OFF
+  float R[12];
+#pragma unroll
+  for (int r = 0; r < 3; ++r) {
+    const float q0 = Q[r * 4 + 0], q1 = Q[r * 4 + 1], q2 = Q[r * 4 + 2], q3 = Q[r * 4 + 3];
+    R[r * 4 + 0] = q0 * P[0] + q1 * P[4] + q2 * P[8];
+    R[r * 4 + 1] = q0 * P[1] + q1 * P[5] + q2 * P[9];
+    R[r * 4 + 2] = q0 * P[2] + q1 * P[6] + q2 * P[10];
+    R[r * 4 + 3] = q0 * P[3] + q1 * P[7] + q2 * P[11] + q3;
+  }
+#pragma unroll
+  for (int e = 0; e < 12; ++e) P[e] = active ? R[e] : P[e];
+}
+
+// One step of the suffix sum of a 6-vector along a chain (row_shl:OFF).
+template <int OFF>
+__device__ __forceinline__ void suffix_step(float* W, bool active) {
+#pragma unroll
+  for (int e = 0; e < 6; ++e) {
+    const float v = dpp<0x100 + OFF>(W[e]);
+    W[e] = active ? W[e] + v : W[e];
+  }
+}
+
+// Pose of this lane's link at its joint value q: the local transform
+// F_l Rz(q) from the Tab.6 closed form (columns 0 and 1 mix, 2 and 3 are
+// F's), then the prefix product along the chain (pos = lanes past the chain
+// start).  Lanes without a link hold the identity.
+template <int LPE>
+__device__ __forceinline__ void link_pose(const float4& f0, const float4& f1, const float4& f2, bool on, int pos,
+                                          float q, float* T) {
+  const float sn = __sinf(q), cs = __cosf(q);
+  T[0] = f0.x * cs + f0.y * sn;  T[1] = f0.y * cs - f0.x * sn;  T[2] = f0.z;  T[3] = f0.w;
+  T[4] = f1.x * cs + f1.y * sn;  T[5] = f1.y * cs - f1.x * sn;  T[6] = f1.z;  T[7] = f1.w;
+  T[8] = f2.x * cs + f2.y * sn;  T[9] = f2.y * cs - f2.x * sn;  T[10] = f2.z; T[11] = f2.w;
+  if (!on) identity(T);
+  scan_step<1>(T, pos >= 1);
+  scan_step<2>(T, pos >= 2);
+  scan_step<4>(T, pos >= 4);
+  if (LPE > 8) scan_step<8>(T, pos >= 8);
+}
+
+// Lane l of an evaluation owns link l (its pose, sphere ball, joint and
+// pose terms); an evaluation takes LPE lanes (8 or 16, one per link) times H
+// copies that split the world's cuboids, and a wave holds 64 / (LPE H)
+// evaluations, so everything an evaluation needs stays inside one wave: the
+// four waves of a workgroup only share the staged rows, tables and cuboid
+// tile (one barrier per tile).
+//
+// What bounds this kernel is the vector work on (sphere, cuboid) pairs.  Of
+// the M N pairs of an evaluation only a few per cent lie within r + eta, but
+// which ones differs from lane to lane, so a loop over cuboids that the
+// whole wave walks runs the exact distance for nearly every pair that any of
+// its lanes needs.  The pairs are therefore compacted in three steps, each
+// spreading its work over the wave's 64 lanes through queues in LDS:
+//   1. (link, cuboid) pairs, one per lane: the ball around the link's
+//      spheres over all the wave's evaluations against the cuboid;
+//   2. (evaluation, link, cuboid), one per lane: the evaluation's own ball;
+//   3. (evaluation, link, cuboid) items, one per lane (several lanes per item,
+//      each with a share of the spheres, when few are left): the face test
+//      of every sphere of the link and, where it passes, the exact term.
+// With swept collision the exact term carries the trace and is long enough
+// to compact again: the spheres that pass the face test go through a second
+// queue, one (sphere, cuboid) pair per lane.
+// The lanes' sums go back to the owners (evaluation, link) through an LDS
+// row per lane: each owner finds its rows from six ballots of the owners'
+// bits and adds them in lane order, so the results are deterministic.  (LDS
+// float atomics cost 194 cycles per wave instruction on gfx950, whatever the
+// addresses: eight of them per 64 pairs bounded this kernel, 411 us against
+// the figure below on 524288 inverse-kinematics evaluations.)
+// The culls are exact: the signed distance is 1-Lipschitz and max(|p| - h)
+// bounds it from below, so a pair they drop adds no cost and cannot lower the
+// clearance clamped at eta.
+//
+// Measured, us per launch (cost and gradient of every candidate), this layout
+// with its best number of copies against the best wave-per-link layout:
+//   524288 single configurations, 40 cuboids (4096 x 32 seeds, K = 4)  280 / 634
+//   64 problems, 84616 rows, 5 to 200 cuboids each, K = 4              163 / 250
+//   two arms, 120 spheres, 500 cuboids, swept, 6144 rows, K = 4        572 / 1101
+//   the same without the sweep                                         247 / 304
+//   128 seeds x 32, 40 cuboids, K = 8                                  17.0 / 28.7
+//   32 seeds x 32, 40 cuboids, K = 8                                   12.5 / 12.4
+//   4 seeds x 32, 10 cuboids, K = 4                                    8.3 / 12.4
+// A wave's time is now the kinematics and the joint terms (some 2100 cycles
+// each) and two memory rounds as much as the pairs.
+
+// Compiler fence between LDS writes and reads of different lanes of one wave
+// (the hardware runs a wave's LDS instructions in order).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+// Sum (or minimum) over the H copies of an evaluation: the lanes that differ
+// in the bits from LPE to LPE H / 2.  Every lane gets the same bits.
+template <int BIT>
+__device__ __forceinline__ float lane_xor(float v, int lane) {
+  if constexpr (BIT == 8) return dpp<0x128>(v);    // row_ror:8
+  const auto r = BIT == 16 ? __builtin_amdgcn_permlane16_swap(__float_as_int(v), __float_as_int(v), false, false)
+                           : __builtin_amdgcn_permlane32_swap(__float_as_int(v), __float_as_int(v), false, false);
+  return __int_as_float((int)(lane & BIT ? r[0] : r[1]));
+}
+template <int LPE, int H, typename OP>
+__device__ __forceinline__ float copies_op(float v, OP op) {
+  const int lane = threadIdx.x % kWave;
+  if constexpr (H >= 2) v = op(v, lane_xor<LPE>(v, lane));
+  if constexpr (H >= 4) v = op(v, lane_xor<2 * LPE>(v, lane));
+  if constexpr (H >= 8) v = op(v, lane_xor<4 * LPE>(v, lane));
+  return v;
+}
+// Minimum over the evaluations of a wave: the lanes that differ in the bits
+// from STRIDE (the lanes of an evaluation) on.
+template <int STRIDE>
+__device__ __forceinline__ float evals_min(float v) {
+  if (STRIDE <= 8) v = fminf(v, dpp<0x128>(v));    // row_ror:8
+  if (STRIDE <= 16) v = swap16_min(v);
+  if (STRIDE <= 32) v = swap32_min(v);
+  return v;
+}
+__device__ __forceinline__ int lanes_below(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
+}
+
+constexpr int kLplWaves = kBlock / kWave;
+constexpr int kLplTile = 64;      // cuboids staged per tile
+constexpr int kLplNear = 3 * kWave;   // entries of the near-pair queue (two spheres are tested between checks)
+// float4 between the rows of a staged tile (one more than the cuboids: the
+// four rows of a cuboid, read together, then lie in different banks)
+constexpr int kLplStride = kLplTile + 1;
+constexpr int kLplGroup = 4;      // cuboids tested between queue checks
+constexpr int kLplQueue = kWave - 1 + kLplGroup * kWave;   // entries a queue may hold
+
+// LDS of a lane-per-link workgroup, float offsets (kept a multiple of 4).
+// Shared: rows of x and of d (or the particle variance), limits and start,
+// goals, tool transforms, sphere slots, the cuboid tile [4][kLplStride]
+// float4, in particle mode the draws; then per wave: link poses (and with
+// swept collision the neighbouring poses and the trace's reach), the
+// evaluations' and the links' balls, the lanes' sums, and the queues.
+struct LplLds {
+  int x, d, lim, goal, etf, slot, box, eps, wave, wave_size, total;
+};
+__host__ __device__ inline LplLds lpl_lds(int lpe, int H, int rb, int kb, int D, int maxs, bool sw, bool pm) {
+  LplLds o;
+  const int rs = rb + 8, ow = kWave / H;
+  int at = 0;
+  auto take = [&at](int n) {
+    const int r = at;
+    at += (n + 3) & ~3;
+    return r;
+  };
+  o.x = take(rs * D);
+  o.d = take(rs * D);
+  o.lim = take(3 * D);
+  o.goal = take(kMaxEE * 7);
+  o.etf = take(kMaxEE * 12);
+  o.slot = take(lpe * maxs * 4);
+  o.box = take(kLplStride * 16);
+  o.eps = take(pm ? kb * rs * D : 0);
+  o.wave = at;
+  o.wave_size = (sw ? 36 : 12) * ow + (sw ? (ow + 3) / 4 * 4 : 0) + 4 * ow + 4 * lpe + 8 * (kWave + 2) +
+                (sw ? kLplNear : 0) + (lpe * kLplTile + 2 * kWave) / 2;
+  o.total = at + kLplWaves * o.wave_size;
+  return o;
+}
+
+// One sphere against one cuboid in the box frame: cost, clearance and, with
+// GRAD, the box-frame force b (d cost / d centre) and its moment m about the
+// box origin, all accumulated.  ax.. = |p| - h, m3 their maximum.
+template <bool GRAD>
+__device__ __forceinline__ void pair_term(float px, float py, float pz, float ax, float ay, float az, float m3,
+                                          float r, float w, float eta, float inv_eta, float& cost, float& mc,
+                                          float* b, float* m) {
+  const float qx = fmaxf(ax, 0.0f), qy = fmaxf(ay, 0.0f), qz = fmaxf(az, 0.0f);
+  const float n2 = qx * qx + qy * qy + qz * qz;
+  const bool out = n2 > 0.0f;
+  const float n = __builtin_amdgcn_sqrtf(n2);
+  const float sdf = out ? n : m3;
+  mc = fminf(mc, sdf - r);
+  // Eq.(10): the slope u / eta clamped to [0, 1], the cost its integral
+  const float u = r - sdf + eta;
+  const float slope = fminf(fmaxf(u * inv_eta, 0.0f), 1.0f);
+  cost = fmaf(w * slope, fmaf(-0.5f * eta, slope, u), cost);
+  if (GRAD) {
+    const float f = -w * slope;
+    const float fo = out ? f * __builtin_amdgcn_rcpf(n) : f;
+    // inside: the nearest face, lowest axis on ties
+    const bool ix = ax == m3, iy = !ix && ay == m3;
+    const float vx = fo * (out ? qx : ix ? 1.0f : 0.0f);
+    const float vy = fo * (out ? qy : iy ? 1.0f : 0.0f);
+    const float vz = fo * (out ? qz : (ix || iy) ? 0.0f : 1.0f);
+    const float gx = px >= 0.0f ? vx : -vx, gy = py >= 0.0f ? vy : -vy, gz = pz >= 0.0f ? vz : -vz;
+    b[0] += gx; b[1] += gy; b[2] += gz;
+    m[0] = fmaf(py, gz, fmaf(-pz, gy, m[0]));
+    m[1] = fmaf(pz, gx, fmaf(-px, gz, m[1]));
+    m[2] = fmaf(px, gy, fmaf(-py, gx, m[2]));
+  }
+}
+
+// The trace toward one neighbouring waypoint (Alg.11-12) in the box frame:
+// direction u (unscaled), from p with distance sdf.
+template <bool GRAD>
+__device__ __forceinline__ void trace_term(float ux, float uy, float uz, int steps, float px, float py, float pz,
+                                           const float4& Hh, float sdf, float r, float w, float eta, float inv_eta,
+                                           float& cost, float* b) {
+  const float rh = r + eta;
+  const float len = sqrtf(ux * ux + uy * uy + uz * uz);
+  const float half = 0.5f * len;
+  float j = sdf < rh ? rh : sdf - rh;
+  if (!(len > 0.0f && j < half)) return;
+  const float il = 1.0f / len;
+  ux *= il; uy *= il; uz *= il;
+  for (int st = 0; st < steps && j < half; ++st) {
+    const float qx = fmaf(j, ux, px), qy = fmaf(j, uy, py), qz = fmaf(j, uz, pz);
+    float s2;
+    if (GRAD) {
+      float gx, gy, gz;
+      s2 = box_sdf(qx, qy, qz, fabsf(qx) - Hh.x, fabsf(qy) - Hh.y, fabsf(qz) - Hh.z, gx, gy, gz);
+      dc_term_box(s2, gx, gy, gz, r, w, eta, inv_eta, cost, b[0], b[1], b[2]);
+    } else {
+      s2 = box_dist(fabsf(qx) - Hh.x, fabsf(qy) - Hh.y, fabsf(qz) - Hh.z);
+      dc_cost(s2, r, w, eta, inv_eta, cost);
+    }
+    j += s2 - rh > 0.0f ? s2 - rh : rh;
+  }
+}
+
+template <int LPE, int H, bool CAND, bool GRAD, bool SW>
+__global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
+  constexpr int EPW = kWave / (LPE * H);           // evaluations per wave
+  constexpr int OW = EPW * LPE;                    // owners (evaluation, link) per wave
+  extern __shared__ float s_mem[];
+  warm_kernargs<sizeof(EvalArgs)>();
+
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int lane = tid % kWave;
+  const int l = lane % LPE, sub = lane / LPE % H, ew = lane / (LPE * H);
+  const int owner = ew * LPE + l;
+  const int D = a.rb.dof, L = a.rb.n_links, maxs = a.ln.maxs, n_ee = a.rb.n_ee;
+  const int KB = a.ln.kb, RB = a.ln.rb;            // candidates and rows per workgroup (KB RB evaluations)
+  const int bx = blockIdx.x;
+
+  // ---- this workgroup's problem: by arithmetic when all problems have one
+  //      size, else from the table of first workgroups (64 entries a step) ----
+  int p = 0, c = bx;
+  if (a.ln.uni_rows > 0) {
+    if (a.P > 1) {
+      const int cpp = (a.ln.uni_rows + RB - 1) / RB;
+      p = bx / cpp;
+      c = bx - p * cpp;
+    }
+  } else {
+    int lo = 0, n = a.P;                            // the last p in [lo, lo + n) with prefix[p] <= bx
+    while (n > 1) {
+      const int st = (n + kWave - 1) / kWave;
+      const int i = lo + min(lane * st, n - 1);
+      const bool le = lane * st < n && a.chunk_prefix[i] <= bx;
+      const int k = __popcll(__ballot(le)) - 1;
+      lo += k * st;
+      n = min(st, n - k * st);
+    }
+    p = __builtin_amdgcn_readfirstlane(lo);
+    c = bx - a.chunk_prefix[p];
+  }
+  int S, T, row0, w0, w1;
+  if (a.wl.one.S > 0) {
+    S = a.wl.one.S; T = a.wl.one.T; row0 = 0; w0 = a.wl.one.box_lo; w1 = a.wl.one.box_hi;
+  } else {
+    cv4i* pr = (cv4i*)(a.prob + p);
+    const v4i p0 = pr[0], p1 = pr[1];
+    S = p0.x; T = p0.y; row0 = p0.w; w0 = p1.y; w1 = p1.z;
+  }
+  Problem pb;
+  pb.S = S; pb.T = T; pb.world = 0; pb.row0 = row0; pb.seed0 = 0; pb.box_lo = w0; pb.box_hi = w1; pb.pad = 0;
+  const int nrows = S * T, first = c * RB;         // this workgroup's first row within the problem
+
+  // evaluation of this lane: candidates of a row side by side
+  const int ei = wave * EPW + ew;
+  const int k = blockIdx.y * KB + ei % KB;
+  const int rloc = first + ei / KB;
+  const bool valid = rloc < nrows;
+  const int rl = valid ? rloc : nrows - 1;
+  const int t = rl % T;                            // waypoint t + 1 of its seed
+  const int row = row0 + rl;
+  const bool pm = CAND && !GRAD && a.var != nullptr;
+
+  const LplLds o = lpl_lds(LPE, H, RB, KB, D, maxs, SW, pm);
+  float* s_x = s_mem + o.x;
+  float* s_d = s_mem + o.d;
+  float* s_lim = s_mem + o.lim;
+  float* s_goal = s_mem + o.goal;
+  float* s_etf = s_mem + o.etf;
+  float4* s_slot = reinterpret_cast<float4*>(s_mem + o.slot);
+  float4* s_box = reinterpret_cast<float4*>(s_mem + o.box);
+  float* s_eps = s_mem + o.eps;
+  float* s_w = s_mem + o.wave + wave * o.wave_size;
+  float4* s_T = reinterpret_cast<float4*>(s_w);                            // [3 or 9][OW]
+  float4* s_ball = s_T + (SW ? 9 : 3) * OW;                                // [OW]
+  float4* s_lball = s_ball + OW;                                           // [LPE]
+  float4* s_res = s_lball + LPE;                                           // [2][kWave + 2]
+  unsigned* s_nq = reinterpret_cast<unsigned*>(s_res + 2 * (kWave + 2));   // [kLplNear] (SW)
+  float* s_ext = reinterpret_cast<float*>(s_nq + (SW ? kLplNear : 0));     // [OW] (SW)
+  unsigned short* s_pq = reinterpret_cast<unsigned short*>(s_ext + (SW ? (OW + 3) / 4 * 4 : 0));   // [LPE kLplTile]
+  unsigned short* s_q = s_pq + LPE * kLplTile;                             // [2 kWave]
+
+  // ---- one round of loads: this lane's link tables, and the staging ----
+  const int lj = l < L ? l : 0;
+  const v4i info = *(const v4i*)(a.ln.info + l);   // chain start, chain end, spheres, end effector
+  const float4 F0 = reinterpret_cast<const float4*>(a.rb.fixed_tf + lj * 12)[0];
+  const float4 F1 = reinterpret_cast<const float4*>(a.rb.fixed_tf + lj * 12)[1];
+  const float4 F2 = reinterpret_cast<const float4*>(a.rb.fixed_tf + lj * 12)[2];
+  const float4 bl = a.wl.ball[lj * kWlBalls];
+  const int r_lo = max(row0, row0 + first - 4);
+  const int r_hi = min(row0 + nrows - 1, row0 + first + RB - 1 + 4);
+  const int n_st = (r_hi - r_lo + 1) * D;
+  const float* dsrc = pm ? a.var : a.d;
+  for (int i = tid; i < n_st; i += kBlock) {
+    const float xv = a.x[(size_t)r_lo * D + i];
+    const float dv = CAND ? dsrc[(size_t)r_lo * D + i] : 0.0f;
+    s_x[i] = xv;
+    if (CAND) s_d[i] = dv;
+  }
+  if (tid < 3 * D) s_lim[tid] = tid < D ? a.rb.q_lo[tid] : tid < 2 * D ? a.rb.q_hi[tid - D] : a.q_start[(size_t)p * D + tid - 2 * D];
+  else if (tid >= kWave && tid < kWave + n_ee * 7) s_goal[tid - kWave] = a.goal[(size_t)p * n_ee * 7 + tid - kWave];
+  else if (tid >= 2 * kWave && tid < 2 * kWave + n_ee * 12) s_etf[tid - 2 * kWave] = a.rb.ee_tf[tid - 2 * kWave];
+  for (int i = tid; i < LPE * maxs; i += kBlock) s_slot[i] = a.ln.sphere[i];
+  auto stage_tile = [&](int tl) {
+    const int nb = min(kLplTile, w1 - tl);
+    const float4* src = reinterpret_cast<const float4*>(a.box + tl);
+    for (int i = tid; i < 4 * nb; i += kBlock) s_box[(i & 3) * kLplStride + (i >> 2)] = src[i];
+  };
+  if (w0 < w1) stage_tile(w0);
+  if (pm) {
+    // the draws of every particle of the workgroup over its rows: from memory
+    // or made here, one Philox block per four elements of [rows][D]
+    const int rs = RB + 8, k0 = blockIdx.y * KB;
+    if (a.d) {
+      for (int i = tid; i < KB * n_st; i += kBlock) {
+        const int kk = i / n_st, e = i - kk * n_st;
+        s_eps[kk * rs * D + e] = a.d[(size_t)(k0 + kk) * a.d_stride + (size_t)r_lo * D + e];
+      }
+    } else {
+      const long long e_lo = (long long)r_lo * D, e_hi = e_lo + n_st;
+      const long long q_lo = e_lo >> 2;
+      const int nq = (int)(((e_hi + 3) >> 2) - q_lo);
+      for (int i = tid; i < nq * KB; i += kBlock) {
+        const int kk = i / nq;
+        const long long q = q_lo + (i - kk * nq);
+        float w4[4];
+        philox_draws4(a.pm_seed, k0 + kk, a.pm_it, (uint64_t)q, w4);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const long long e = 4 * q + u;
+          if (e >= e_lo && e < e_hi) s_eps[kk * rs * D + (int)(e - e_lo)] = w4[u];
+        }
+      }
+    }
+  }
+  __syncthreads();
+
+  const float alpha = CAND ? a.alpha[k < kMaxK ? k : 0] : 0.0f;
+  const int eps0 = pm ? (k - (int)blockIdx.y * KB) * (RB + 8) * D : 0;
+  // candidate value of joint j at row r: clip(x + alpha d) for a line-search
+  // candidate, clip(x + sqrt(var) eps_k) for a particle
+  auto qval = [&](int r, int j) -> float {
+    const int i = (r - r_lo) * D + j;
+    float v = s_x[i];
+    if (CAND) {
+      if (pm) v = fmaf(sqrtf(s_d[i]), s_eps[eps0 + i], v);
+      else v = fmaf(alpha, s_d[i], v);
+      v = fminf(fmaxf(v, s_lim[j]), s_lim[D + j]);
+    }
+    return v;
+  };
+
+  // ---- kinematics: the local transform F_l Rz(q_l) (Tab.6) and the prefix
+  //      product along the chain, for this waypoint (and its neighbours) ----
+  const bool on = l < L;
+  const int pos = l - info.x;
+  const float ql = qval(row, lj);
+  float Tm[12];
+  link_pose<LPE>(F0, F1, F2, on, pos, ql, Tm);
+  float ext = 0.0f;
+  const bool sweep = SW && T > 1;
+  if constexpr (SW) {
+    // link poses at the neighbouring waypoints (the start before waypoint 1;
+    // none after the last: its own pose, a segment of length zero)
+    float Tp[12], Tn[12];
+    if (sweep) {
+      const bool nxt = t + 1 < T;
+      const float qp = t >= 1 ? qval(row - 1, lj) : s_lim[2 * D + lj];
+      const float qn = nxt ? qval(row + 1, lj) : ql;
+      link_pose<LPE>(F0, F1, F2, on, pos, qp, Tp);
+      link_pose<LPE>(F0, F1, F2, on, pos, qn, Tn);
+#pragma unroll
+      for (int e = 0; e < 12; ++e) Tn[e] = nxt ? Tn[e] : Tm[e];
+      // the cull's reach: half the longest segment over the link's spheres
+      // (slightly widened so rounding never culls a sample the trace takes)
+      float l2 = 0.0f;
+      for (int s = 0; s < info.z; ++s) {
+        const float4 ls = s_slot[l * maxs + s];
+        auto seg2 = [&](const float* N) {
+          const float ux = (N[0] - Tm[0]) * ls.x + (N[1] - Tm[1]) * ls.y + (N[2] - Tm[2]) * ls.z + (N[3] - Tm[3]);
+          const float uy = (N[4] - Tm[4]) * ls.x + (N[5] - Tm[5]) * ls.y + (N[6] - Tm[6]) * ls.z + (N[7] - Tm[7]);
+          const float uz = (N[8] - Tm[8]) * ls.x + (N[9] - Tm[9]) * ls.y + (N[10] - Tm[10]) * ls.z + (N[11] - Tm[11]);
+          return ux * ux + uy * uy + uz * uz;
+        };
+        l2 = fmaxf(l2, fmaxf(seg2(Tp), seg2(Tn)));
+      }
+      ext = 0.5f * sqrtf(l2) * 1.001f + 1e-6f;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 12; ++e) Tp[e] = Tn[e] = Tm[e];
+    }
+    if (sub == 0) {
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        s_T[(3 + r) * OW + owner] = make_float4(Tp[4 * r], Tp[4 * r + 1], Tp[4 * r + 2], Tp[4 * r + 3]);
+        s_T[(6 + r) * OW + owner] = make_float4(Tn[4 * r], Tn[4 * r + 1], Tn[4 * r + 2], Tn[4 * r + 3]);
+      }
+      s_ext[owner] = ext;
+    }
+  }
+  if (sub == 0) {
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+      s_T[r * OW + owner] = make_float4(Tm[4 * r], Tm[4 * r + 1], Tm[4 * r + 2], Tm[4 * r + 3]);
+  }
+  // the ball around the link's spheres, widened slightly so rounding never
+  // drops a cuboid that matters (a lane without spheres never passes)
+  const float eta = a.pr.eta, inv_eta = 1.0f / fmaxf(eta, 1e-30f), wc = a.pr.w_coll;
+  const float cbx = Tm[0] * bl.x + Tm[1] * bl.y + Tm[2] * bl.z + Tm[3];
+  const float cby = Tm[4] * bl.x + Tm[5] * bl.y + Tm[6] * bl.z + Tm[7];
+  const float cbz = Tm[8] * bl.x + Tm[9] * bl.y + Tm[10] * bl.z + Tm[11];
+  const float rball = on && info.z > 0 ? (bl.w + eta) * 1.0001f + 1e-6f + ext : -1e30f;
+  if (sub == 0) s_ball[owner] = make_float4(cbx, cby, cbz, rball);
+  if (EPW > 1) {
+    // the link's ball over the wave's evaluations: centre of the bounding box
+    // of their centres, half its diagonal more (widened as above)
+    const float lx = evals_min<LPE * H>(cbx), ly = evals_min<LPE * H>(cby), lz = evals_min<LPE * H>(cbz);
+    const float ux = -evals_min<LPE * H>(-cbx), uy = -evals_min<LPE * H>(-cby), uz = -evals_min<LPE * H>(-cbz);
+    const float rm = -evals_min<LPE * H>(-rball);
+    const float hx = ux - lx, hy = uy - ly, hz = uz - lz;
+    if (lane < LPE)
+      s_lball[lane] = make_float4(0.5f * (lx + ux), 0.5f * (ly + uy), 0.5f * (lz + uz),
+                                  rm + 0.5f * sqrtf(hx * hx + hy * hy + hz * hz) * 1.0001f + 1e-6f);
+  } else if (lane < LPE) {
+    s_lball[lane] = make_float4(cbx, cby, cbz, rball);
+  }
+  wave_lds_fence();
+
+  // ---- the near pairs ----
+  const int used = a.ln.used;                      // most spheres on any link
+  // this lane's sums as an owner (copy sub of an evaluation adds the rows of
+  // its share of the lanes): cost, clearance, force and moment about the
+  // world origin
+  float acc[8] = {0.0f, eta, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+  // the lanes' v (owner ow, where act) added to their owners' sums
+  auto deliver = [&](bool act, int ow, const float* v) {
+    s_res[lane] = make_float4(v[0], v[1], v[2], v[3]);
+    if (GRAD) s_res[kWave + 2 + lane] = make_float4(v[4], v[5], v[6], v[7]);
+    // the rows of this owner: those whose owner agrees in all six bits
+    const uint64_t va = __ballot(act);
+    unsigned mlo = (unsigned)va, mhi = (unsigned)(va >> 32);
+#pragma unroll
+    for (int bit = 0; bit < 6; ++bit) {
+      if ((1 << bit) >= OW) break;
+      const uint64_t ob = __ballot((ow >> bit) & 1);
+      const unsigned mine = (owner >> bit) & 1 ? ~0u : 0u;
+      mlo &= ~((unsigned)ob ^ mine);
+      mhi &= ~((unsigned)(ob >> 32) ^ mine);
+    }
+    wave_lds_fence();
+    auto add = [&](unsigned i) {
+      const float4 a4 = s_res[i];
+      acc[0] += a4.x;
+      acc[1] = fminf(acc[1], a4.y);
+      if (GRAD) {
+        const float4 b4 = s_res[kWave + 2 + i];
+        acc[2] += a4.z; acc[3] += a4.w;
+        acc[4] += b4.x; acc[5] += b4.y; acc[6] += b4.z; acc[7] += b4.w;
+      }
+    };
+    // (no row left: row kWave, which holds nothing)
+    if constexpr (H == 1) {
+      while (__ballot((mlo | mhi) != 0)) {
+        const unsigned i0 = min((unsigned)(__ffs(mlo) - 1), (unsigned)kWave);
+        const unsigned i1 = min((unsigned)(__ffs(mhi) - 1), 32u) + 32;
+        mlo &= mlo - 1;
+        mhi &= mhi - 1;
+        add(i0);
+        add(i1);
+      }
+    } else {
+      constexpr int SH = kWave / H;                // rows of a copy's share
+      unsigned mw = sub * SH < 32 ? mlo >> (sub * SH & 31) : mhi >> (sub * SH & 31);
+      if (SH < 32) mw &= (1u << (SH & 31)) - 1;
+      while (__ballot(mw != 0)) {
+        const unsigned i = mw ? (unsigned)(__ffs(mw) - 1 + sub * SH) : (unsigned)kWave;
+        mw &= mw - 1;
+        add(i);
+      }
+    }
+    wave_lds_fence();
+  };
+  if (lane < 2) {
+    s_res[kWave + lane] = make_float4(0.0f, 3.0e38f, 0.0f, 0.0f);
+    s_res[2 * kWave + 2 + lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  }
+  int nnq = 0;                                     // near pairs pending (SW)
+  // one (owner, sphere, cuboid) per lane: the exact term and the trace (SW)
+  auto near_chunk = [&](int base, int n) {
+    if constexpr (SW) {
+      const bool act = lane < n;
+      const unsigned it = act ? s_nq[base + lane] : 0;
+      const int ow = it & 63, ob = (it >> 6) & 63, sl = it >> 12;
+      const float4 A0 = s_box[ob], A1 = s_box[kLplStride + ob], A2 = s_box[2 * kLplStride + ob],
+                   Hh = s_box[3 * kLplStride + ob];
+      const float4 t0 = s_T[ow], t1 = s_T[OW + ow], t2 = s_T[2 * OW + ow];
+      const float4 ls = s_slot[(ow % LPE) * maxs + sl];
+      const float cx = t0.x * ls.x + t0.y * ls.y + t0.z * ls.z + t0.w;
+      const float cy = t1.x * ls.x + t1.y * ls.y + t1.z * ls.z + t1.w;
+      const float cz = t2.x * ls.x + t2.y * ls.y + t2.z * ls.z + t2.w;
+      const float px = fmaf(A0.x, cx, fmaf(A0.y, cy, fmaf(A0.z, cz, A0.w)));
+      const float py = fmaf(A1.x, cx, fmaf(A1.y, cy, fmaf(A1.z, cz, A1.w)));
+      const float pz = fmaf(A2.x, cx, fmaf(A2.y, cy, fmaf(A2.z, cz, A2.w)));
+      const float ax = fabsf(px) - Hh.x, ay = fabsf(py) - Hh.y, az = fabsf(pz) - Hh.z;
+      float cost = 0.0f, b[3] = {0.0f, 0.0f, 0.0f}, gx, gy, gz, sdf;
+      if (GRAD) {
+        sdf = box_sdf(px, py, pz, ax, ay, az, gx, gy, gz);
+        dc_term_box(sdf, gx, gy, gz, ls.w, wc, eta, inv_eta, cost, b[0], b[1], b[2]);
+      } else {
+        sdf = box_dist(ax, ay, az);
+        dc_cost(sdf, ls.w, wc, eta, inv_eta, cost);
+      }
+      const float clr = sdf - ls.w;
+      if (act) {
+#pragma unroll
+        for (int side = 1; side < 3; ++side) {
+          // the segment from the neighbouring poses' difference, box frame
+          float u[3];
+#pragma unroll
+          for (int r = 0; r < 3; ++r) {
+            const float4 tc = r == 0 ? t0 : r == 1 ? t1 : t2, tn = s_T[(3 * side + r) * OW + ow];
+            u[r] = (tn.x - tc.x) * ls.x + (tn.y - tc.y) * ls.y + (tn.z - tc.z) * ls.z + (tn.w - tc.w);
+          }
+          trace_term<GRAD>(A0.x * u[0] + A0.y * u[1] + A0.z * u[2], A1.x * u[0] + A1.y * u[1] + A1.z * u[2],
+                           A2.x * u[0] + A2.y * u[1] + A2.z * u[2], a.pr.sweep_steps, px, py, pz, Hh, sdf, ls.w, wc,
+                           eta, inv_eta, cost, b);
+        }
+      }
+      const float fx = A0.x * b[0] + A1.x * b[1] + A2.x * b[2];
+      const float fy = A0.y * b[0] + A1.y * b[1] + A2.y * b[2];
+      const float fz = A0.z * b[0] + A1.z * b[1] + A2.z * b[2];
+      const float v[8] = {cost, clr, fx, fy, fz, cy * fz - cz * fy, cz * fx - cx * fz, cx * fy - cy * fx};
+      deliver(act, ow, v);
+    }
+  };
+  // n (owner, cuboid) items, one per lane, or 2, 4 or 8 lanes per item with
+  // a share of the link's spheres each
+  auto link_chunk = [&](const unsigned short* q, int n) {
+    const int sh = n > 32 ? 0 : n > 16 ? 1 : n > 8 ? 2 : 3, per = kWave >> sh;
+    const int ii = lane & (per - 1);
+    const bool act = ii < n;
+    const unsigned it = act ? q[ii] : 0;
+    const int ow = it & 63, ob = it >> 6;
+    const float4 A0 = s_box[ob], A1 = s_box[kLplStride + ob], A2 = s_box[2 * kLplStride + ob],
+                 Hh = s_box[3 * kLplStride + ob];
+    const float4 t0 = s_T[ow], t1 = s_T[OW + ow], t2 = s_T[2 * OW + ow];
+    const float4* sl = s_slot + (ow % LPE) * maxs;
+    const float reach = act ? eta + (SW ? s_ext[ow] : 0.0f) : -1e30f;
+    const int s1 = lane >> (6 - sh);               // this lane's spheres: s1, s1 + (1 << sh), ..
+    float cost = 0.0f, mc = 3.0e38f, b[3] = {0.0f, 0.0f, 0.0f}, m[3] = {0.0f, 0.0f, 0.0f};
+    // (the face test; an unused slot's radius is -1e30: it never passes)
+    auto test = [&](int s, float4& ls, float* p, float& m3) -> bool {
+      ls = sl[min(s, used - 1)];
+      const float cx = t0.x * ls.x + t0.y * ls.y + t0.z * ls.z + t0.w;
+      const float cy = t1.x * ls.x + t1.y * ls.y + t1.z * ls.z + t1.w;
+      const float cz = t2.x * ls.x + t2.y * ls.y + t2.z * ls.z + t2.w;
+      p[0] = fmaf(A0.x, cx, fmaf(A0.y, cy, fmaf(A0.z, cz, A0.w)));
+      p[1] = fmaf(A1.x, cx, fmaf(A1.y, cy, fmaf(A1.z, cz, A1.w)));
+      p[2] = fmaf(A2.x, cx, fmaf(A2.y, cy, fmaf(A2.z, cz, A2.w)));
+      m3 = fmaxf(fabsf(p[0]) - Hh.x, fmaxf(fabsf(p[1]) - Hh.y, fabsf(p[2]) - Hh.z));
+      return s < used && m3 < ls.w + reach;
+    };
+    for (int s0 = 0; s0 < used; s0 += 2 << sh) {
+      const int sa = s0 + s1, sb = sa + (1 << sh);
+      float4 la, lb;
+      float pa[3], pb[3], ma, mb;
+      const bool ha = test(sa, la, pa, ma), hb = test(sb, lb, pb, mb);
+      if constexpr (SW) {
+        const uint64_t ba = __ballot(ha), bb = __ballot(hb);
+        if (ha) s_nq[nnq + lanes_below(ba)] = it | sa << 12;
+        nnq += __popcll(ba);
+        if (hb) s_nq[nnq + lanes_below(bb)] = it | sb << 12;
+        nnq += __popcll(bb);
+        wave_lds_fence();
+        while (nnq >= kWave) {
+          nnq -= kWave;
+          near_chunk(nnq, kWave);
+        }
+      } else {
+        if (ha)
+          pair_term<GRAD>(pa[0], pa[1], pa[2], fabsf(pa[0]) - Hh.x, fabsf(pa[1]) - Hh.y, fabsf(pa[2]) - Hh.z, ma, la.w,
+                          wc, eta, inv_eta, cost, mc, b, m);
+        if (hb)
+          pair_term<GRAD>(pb[0], pb[1], pb[2], fabsf(pb[0]) - Hh.x, fabsf(pb[1]) - Hh.y, fabsf(pb[2]) - Hh.z, mb, lb.w,
+                          wc, eta, inv_eta, cost, mc, b, m);
+      }
+    }
+    if constexpr (!SW) {
+      // force and moment about the world origin (the box origin is at
+      // -A^T (A0.w, A1.w, A2.w)); items no sphere of which passed add nothing
+      const bool some = mc < 3.0e38f;
+      if (__ballot(some)) {
+        const float fx = A0.x * b[0] + A1.x * b[1] + A2.x * b[2];
+        const float fy = A0.y * b[0] + A1.y * b[1] + A2.y * b[2];
+        const float fz = A0.z * b[0] + A1.z * b[1] + A2.z * b[2];
+        const float ox = -(A0.x * A0.w + A1.x * A1.w + A2.x * A2.w);
+        const float oy = -(A0.y * A0.w + A1.y * A1.w + A2.y * A2.w);
+        const float oz = -(A0.z * A0.w + A1.z * A1.w + A2.z * A2.w);
+        const float v[8] = {cost, mc, fx, fy, fz,
+                            A0.x * m[0] + A1.x * m[1] + A2.x * m[2] + (oy * fz - oz * fy),
+                            A0.y * m[0] + A1.y * m[1] + A2.y * m[2] + (oz * fx - ox * fz),
+                            A0.z * m[0] + A1.z * m[1] + A2.z * m[2] + (ox * fy - oy * fx)};
+        deliver(some, ow, v);
+      }
+    }
+  };
+
+  // ---- world collision (Eq.(10)/(11), summed over cuboids and spheres) ----
+  for (int tl = w0; tl < w1; tl += kLplTile) {
+    if (tl > w0) {
+      __syncthreads();
+      stage_tile(tl);
+      __syncthreads();
+    }
+    const int nb = min(kLplTile, w1 - tl);
+    // the cuboid's distance bound from a ball's centre against its radius
+    auto reaches = [&](const float4& c4, int ob) -> bool {
+      const float4 A0 = s_box[ob], A1 = s_box[kLplStride + ob], A2 = s_box[2 * kLplStride + ob],
+                   Hh = s_box[3 * kLplStride + ob];
+      const float px = fmaf(A0.x, c4.x, fmaf(A0.y, c4.y, fmaf(A0.z, c4.z, A0.w)));
+      const float py = fmaf(A1.x, c4.x, fmaf(A1.y, c4.y, fmaf(A1.z, c4.z, A1.w)));
+      const float pz = fmaf(A2.x, c4.x, fmaf(A2.y, c4.y, fmaf(A2.z, c4.z, A2.w)));
+      return fmaxf(fabsf(px) - Hh.x, fmaxf(fabsf(py) - Hh.y, fabsf(pz) - Hh.z)) < c4.w;
+    };
+    // 1. (link, cuboid) pairs i = l nb + o (the division by multiplication:
+    //    exact for i < 2^10, nb <= 64)
+    const int n_lo = L * nb;
+    const unsigned magic = ((1u << 20) + nb - 1) / nb;
+    int np = 0;
+#pragma unroll 2
+    for (int i0 = 0; i0 < n_lo; i0 += kWave) {
+      const int i = min(i0 + lane, n_lo - 1);
+      const int pl = (i * magic) >> 20, ob = i - pl * nb;
+      const bool hit = reaches(s_lball[pl], ob) && i0 + lane < n_lo;
+      const uint64_t bal = __ballot(hit);
+      if (hit) s_pq[np + lanes_below(bal)] = (unsigned short)(pl | ob << 6);
+      np += __popcll(bal);
+    }
+    wave_lds_fence();
+    // 2. (evaluation, link, cuboid), kWave / EPW pairs a step; then 3.
+    if constexpr (EPW == 1) {
+      for (int i = 0; i < np; i += kWave) link_chunk(s_pq + i, min(kWave, np - i));
+    } else {
+      constexpr int PPS = kWave / EPW;
+      int nq = 0;
+      for (int i0 = 0; i0 < np; i0 += PPS) {
+        const int pj = i0 + lane / EPW;
+        const unsigned it = s_pq[min(pj, np - 1)];
+        const int ow = (lane % EPW) * LPE + (it & 63), ob = it >> 6;
+        const bool hit = reaches(s_ball[ow], ob) && pj < np;
+        const uint64_t bal = __ballot(hit);
+        if (hit) s_q[nq + lanes_below(bal)] = (unsigned short)(ow | ob << 6);
+        nq += __popcll(bal);
+        wave_lds_fence();
+        const bool last = i0 + PPS >= np;
+        while (nq >= kWave || (last && nq > 0)) {
+          const int n = min(nq, kWave);
+          nq -= n;
+          link_chunk(s_q + nq, n);
+        }
+      }
+    }
+    if (SW && nnq > 0) {                           // (the next tile replaces the cuboids)
+      near_chunk(0, nnq);
+      nnq = 0;
+    }
+  }
+
+  // ---- joint l: limit cost (Eq.(17)) and smoothness (Eq.(16)); every lane
+  //      computes (clamped joint), lanes l >= D discard the result ----
+  float cost = 0.0f, gsm = 0.0f;
+  {
+    float jc = 0.0f, js = 0.0f;
+    joint_terms(a, pb, row, t, lj, ql, s_lim[lj], s_lim[D + lj], s_lim[2 * D + lj], qval, jc, js);
+    cost = l < D ? jc : 0.0f;
+    gsm = l < D ? js : 0.0f;
+  }
+  // wrench of this link about the world origin: F = sum of d cost / d point,
+  // M = sum of point x (d cost / d point) (+ pure moments of the pose term)
+  float F[3] = {0.0f, 0.0f, 0.0f}, M[3] = {0.0f, 0.0f, 0.0f};
+  // ---- pose reaching cost at the last waypoint (Eq.(14)) ----
+  if (info.w >= 0 && t == T - 1)
+    pose_term_at(a, s_etf + info.w * 12, s_goal + info.w * 7, info.w, Tm, valid && sub == 0 ? row : -1, cost, F[0],
+                 F[1], F[2], M[0], M[1], M[2]);
+  // the copies' shares of the owner's sums
+  if constexpr (H > 1) {
+#pragma unroll
+    for (int q = 0; q < (GRAD ? 8 : 2); ++q)
+      acc[q] = q == 1 ? copies_op<LPE, H>(acc[q], [](float x, float y) { return fminf(x, y); })
+                      : copies_op<LPE, H>(acc[q], [](float x, float y) { return x + y; });
+  }
+  cost += acc[0];
+  const float mc = acc[1];
+
+  // ---- adjoint: suffix sum of link wrenches, projection on joint l's axis ----
+  float gradj = 0.0f;
+  if (GRAD) {
+    float W[6];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      W[q] = F[q] + acc[2 + q];
+      W[3 + q] = M[q] + acc[5 + q];
+    }
+    const int left = info.y - 1 - l;               // links after this one on its chain
+    suffix_step<1>(W, left >= 1);
+    suffix_step<2>(W, left >= 2);
+    suffix_step<4>(W, left >= 4);
+    if (LPE > 8) suffix_step<8>(W, left >= 8);
+    // revolute z (Tab.7): joint axis z and origin o are columns 2 and 3 of the
+    // link pose; d/dq = z . (M - o x F)
+    const float ux = W[3] - (Tm[7] * W[2] - Tm[11] * W[1]);
+    const float uy = W[4] - (Tm[11] * W[0] - Tm[3] * W[2]);
+    const float uz = W[5] - (Tm[3] * W[1] - Tm[7] * W[0]);
+    gradj = l < D ? Tm[2] * ux + Tm[6] * uy + Tm[10] * uz + gsm : 0.0f;
+  }
+
+  const float csum = group_sum<LPE>(cost);
+  const float mcmin = group_min<LPE>(mc);
+  float gd = 0.0f;
+  if (CAND && GRAD && l < D) gd = gradj * s_d[(row - r_lo) * D + l];
+  if (CAND && GRAD) gd = group_sum<LPE>(gd);
+  if (valid && sub == 0) {
+    const size_t e = (size_t)k * a.rows + row;
+    if (l == 0) {
+      a.cost_e[e] = csum;
+      if (a.mc_e) a.mc_e[e] = mcmin;
+      if (CAND && GRAD) a.gd_e[e] = gd;
+    }
+    if (GRAD && l < D) a.grad_e[e * D + l] = gradj;
+  }
+}
+
+template <int LPE, int H, bool SW>
+hipError_t launch_eval_sw(const EvalArgs& a, int grid_x, bool cand, bool grad, hipStream_t s) {
+  constexpr int epb = kLplWaves * kWave / (LPE * H);
+  const bool pm = a.var != nullptr;
+  // the workgroup's evaluations are KB candidates (a divisor of K) of RB rows
+  const int K = cand ? a.K : 1;
+  if (a.ln.kb < 1 || a.ln.kb * a.ln.rb != epb || K % a.ln.kb || (pm && (!cand || grad)) || a.ln.lpe != LPE ||
+      a.ln.maxs > 16 || a.ln.used > a.ln.maxs || a.rb.dof > a.rb.n_links || a.rb.n_links > LPE || grid_x < 1)
+    return hipErrorInvalidValue;
+  const dim3 grid(grid_x, K / a.ln.kb), block(kBlock);
+  const size_t lds = (size_t)lpl_lds(LPE, H, a.ln.rb, a.ln.kb, a.rb.dof, a.ln.maxs, SW, pm).total * sizeof(float);
+  auto go = [&](auto kern) -> hipError_t {
+    if (lds > 64 * 1024) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+    }
+    kern<<<grid, block, lds, s>>>(a);
+    return hipGetLastError();
+  };
+  if (cand && grad) return go(eval_kernel<LPE, H, true, true, SW>);
+  if (grad) return go(eval_kernel<LPE, H, false, true, SW>);
+  if (!cand) return go(eval_kernel<LPE, H, false, false, SW>);
+  return go(eval_kernel<LPE, H, true, false, SW>);   // particle costs
+}
+
+template <int LPE, int H>
+hipError_t launch_eval_shape(const EvalArgs& a, int grid_x, bool cand, bool grad, hipStream_t s) {
+  return a.pr.swept ? launch_eval_sw<LPE, H, true>(a, grid_x, cand, grad, s)
+                    : launch_eval_sw<LPE, H, false>(a, grid_x, cand, grad, s);
+}
+
+}  // namespace
+}  // namespace mg

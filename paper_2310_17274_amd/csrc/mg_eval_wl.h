@@ -383,8 +383,8 @@ __device__ __forceinline__ void eval_wl_body(const EvalArgs& a, const FA& fa) {
   const int p = c0.x, e_first = c0.y;
   Problem pb;
   pb.S = c0.z; pb.T = c0.w; pb.world = 0; pb.row0 = c1.z;
-  pb.seed0 = 0; pb.pad0 = 0; pb.pad1 = 0; pb.pad2 = 0;
   const int box_lo = c1.x, box_hi = c1.y, n_e = c1.w;
+  pb.seed0 = 0; pb.box_lo = box_lo; pb.box_hi = box_hi; pb.pad = 0;
   // (this wave's first link: its tables are read with the chunk record)
   const int l0 = HS == 2 ? wave >> 1 : min(wave, L - 1);
   v4i info = *(cv4i*)(a.wl.info + l0);

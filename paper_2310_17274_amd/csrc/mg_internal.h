@@ -35,12 +35,17 @@ struct Params {
   float w_self;
   int n_self;              // self-collision pairs (wave-per-link layout only)
   int speed;               // speed metric (wave-per-link layout only)
+  // reciprocals the joint terms need: 1 / eta2, and of the stencils'
+  // denominators 12 dt, 12 dt^2, 2 dt^3
+  float inv_e2, cv, ca, cj;
 };
 
 // One motion problem of a batch.  Rows are waypoints: seed s of problem p
 // owns rows row0 + s*T .. row0 + (s+1)*T - 1.
 struct Problem {
-  int S, T, world, row0, seed0, pad0, pad1, pad2;
+  int S, T, world, row0, seed0;
+  int box_lo, box_hi;      // the world's cuboids (rewritten by mg_set_worlds)
+  int pad;
 };
 
 // Per seed: first row, horizon, problem.
@@ -64,8 +69,11 @@ struct Robot {
 struct Lanes {
   int lpe;                 // lanes per evaluation: 8 or 16
   int maxs;                // sphere slots per link: 4, 8 or 16
+  int used;                // most spheres on any link (<= maxs)
+  int kb, rb;              // a workgroup's evaluations: kb candidates (dividing K) of rb rows
+  int uni_rows;            // > 0: every problem has this many rows (S T)
   const int4* info;        // [lpe]: chain start lane, chain end lane, spheres, end effector or -1
-  const float4* sphere;    // [lpe][maxs] center in link frame + radius
+  const float4* sphere;    // [lpe][maxs] center in link frame + radius (-1e30: no sphere)
 };
 
 // One 64-evaluation chunk of the wave-per-link layout: its problem, its
@@ -87,7 +95,6 @@ struct WaveLinks {
     int S, T, box_lo, box_hi, n_e;
   } one;
   const int4* info;        // [L]: chain depth, spheres, end effector or -1, 0
-  const int* chain;        // [L][kMaxDof]: links from the root down to l
   const int* joint_rec;    // [D][2]: chain position of joint j (its link's depth - 1) and
                            //   the bit mask of the links whose chain contains it
   const float4* chain_rec; // [L][kMaxDof][4]: fixed transform rows of chain[i], then
@@ -186,13 +193,12 @@ struct EvalArgs {
   Lanes ln;
   WaveLinks wl;
   Params pr;
-  int slices;              // waves that split one evaluation group's cuboids: 1, 2 or 4
+  int slices;              // lane per link: copies of an evaluation that split its cuboids (1, 2, 4, 8)
   const Problem* prob;     // [P]
-  const int* chunk_prefix; // [P+1] workgroups before problem p (for this lane layout)
+  const int* chunk_prefix; // [P+1] workgroups of ln.rb rows before problem p
   int P;
   int rows;
   const Box* box;          // all worlds' cuboids
-  const int* world_off;    // [W+1]
   const float* q_start;    // [P][D]
   const float* goal;       // [P][n_ee][7]
   const float* x;          // [rows][D]
@@ -426,6 +432,14 @@ struct FinalArgs {
 
 // Launchers (mg_kernels.hip).  Each returns the hipError_t of the launch.
 hipError_t launch_eval(const EvalArgs& a, int grid_x, bool cand, bool grad, hipStream_t s);
+// One translation unit per (lanes per evaluation, copies).
+hipError_t launch_eval_l8h1(const EvalArgs& a, int grid_x, bool cand, bool grad, hipStream_t s);
+hipError_t launch_eval_l8h2(const EvalArgs& a, int grid_x, bool cand, bool grad, hipStream_t s);
+hipError_t launch_eval_l8h4(const EvalArgs& a, int grid_x, bool cand, bool grad, hipStream_t s);
+hipError_t launch_eval_l8h8(const EvalArgs& a, int grid_x, bool cand, bool grad, hipStream_t s);
+hipError_t launch_eval_l16h1(const EvalArgs& a, int grid_x, bool cand, bool grad, hipStream_t s);
+hipError_t launch_eval_l16h2(const EvalArgs& a, int grid_x, bool cand, bool grad, hipStream_t s);
+hipError_t launch_eval_l16h4(const EvalArgs& a, int grid_x, bool cand, bool grad, hipStream_t s);
 // wave-per-link layout: grid_x workgroups of 64 evaluations (chunk_prefix
 // counts 64-evaluation chunks of rows x K per problem)
 // fs (or null): the previous choice folded into this launch (cost and

@@ -1,10 +1,6 @@
 // mg_kernels.hip -- gfx950 kernels of the batched trajectory-optimizer hot path.
 //
-// eval_kernel      one launch evaluates cost (and gradient) of every
-//                  (candidate k, waypoint row): FK in registers, sphere-vs-
-//                  cuboid cost with cuboids read as wave-uniform scalar
-//                  loads, joint-limit, smoothness and pose costs, and the
-//                  hand-written adjoint with the chain transforms recomputed.
+// (the evaluation kernels are in mg_eval_lane.h and mg_eval_wl.h)
 // reduce_kernel    per-seed sums of a single evaluation.
 // (select_kernel and lbfgs_kernel, the line-search choice with best
 //  tracking and the two-loop L-BFGS direction, are in mg_solver.h)
@@ -17,7 +13,6 @@
 #include <climits>
 
 #include "mg_device.h"
-#include "mg_eval.h"
 
 namespace mg {
 namespace {
@@ -482,13 +477,14 @@ int blocks_for(size_t n) {
 
 hipError_t launch_eval(const EvalArgs& a, int grid_x, bool cand, bool grad, hipStream_t s) {
   if (a.pr.speed) return hipErrorInvalidValue;   // evaluated by the wave-per-link layout only
-  const int L = a.ln.lpe, S = a.ln.maxs;
-  if (L == 8 && S == 4) return launch_eval_l8s4(a, grid_x, cand, grad, s);
-  if (L == 8 && S == 8) return launch_eval_l8s8(a, grid_x, cand, grad, s);
-  if (L == 8 && S == 16) return launch_eval_l8s16(a, grid_x, cand, grad, s);
-  if (L == 16 && S == 4) return launch_eval_l16s4(a, grid_x, cand, grad, s);
-  if (L == 16 && S == 8) return launch_eval_l16s8(a, grid_x, cand, grad, s);
-  if (L == 16 && S == 16) return launch_eval_l16s16(a, grid_x, cand, grad, s);
+  const int L = a.ln.lpe, H = a.slices;
+  if (L == 8 && H == 1) return launch_eval_l8h1(a, grid_x, cand, grad, s);
+  if (L == 8 && H == 2) return launch_eval_l8h2(a, grid_x, cand, grad, s);
+  if (L == 8 && H == 4) return launch_eval_l8h4(a, grid_x, cand, grad, s);
+  if (L == 8 && H == 8) return launch_eval_l8h8(a, grid_x, cand, grad, s);
+  if (L == 16 && H == 1) return launch_eval_l16h1(a, grid_x, cand, grad, s);
+  if (L == 16 && H == 2) return launch_eval_l16h2(a, grid_x, cand, grad, s);
+  if (L == 16 && H == 4) return launch_eval_l16h4(a, grid_x, cand, grad, s);
   return hipErrorInvalidValue;
 }
 

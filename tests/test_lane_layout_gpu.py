@@ -1,0 +1,64 @@
+"""Lane-per-link evaluation at the sizes where its queues and tables turn
+over: cuboid counts around a tile of 64, candidate counts that do not divide
+a workgroup, one to many spheres per link, ragged last workgroups, many
+problems in the table of first workgroups, crowded worlds that fill the
+queues, and every number of copies.  Cost, gradient, <g, d> and clearance of
+every candidate against the FP64 reference, and twice the same bits."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2310_17274_amd import workloads as wl
+from tests.test_fullsize_gpu import _check_candidates, _direction, _oracle_candidates
+from tests.test_parity_gpu import Case, _dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(robot, counts, seeds, horizon, world, K, slices):
+    worlds = wl.make_worlds(21, counts)
+    batch = wl.make_batch(robot, 22, seeds, horizon, world, noise=0.1)
+    case = Case(robot, worlds, batch, layout=(0, slices))
+    alpha = [float(a) for a in np.linspace(0.05, 1.0, K)]
+    d = _direction(case, 0.1, 23)
+    outs = []
+    for _ in range(2):
+        o = case.ctx.mg_linesearch_eval(case.b, case.q_start, case.goal, case.x, _dev(d), alpha)
+        torch.cuda.synchronize()
+        outs.append([t.cpu().numpy() for t in o])
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)
+    cost, gd, g, mc = outs[0]
+    ref_k = _oracle_candidates(case, case.batch.x0.reshape(-1, robot.dof), d, alpha)
+    _check_candidates(case, cost, gd, g, mc, ref_k, d)
+
+
+@pytest.mark.parametrize("slices", [0, 1, 2, 4])
+@pytest.mark.parametrize("n_box", [1, 63, 64, 65, 130])
+def test_cuboid_tiles(n_box, slices):
+    _check(wl.make_arm(seed=0, n_spheres=52), [n_box], [3], [7], [0], 4, slices)
+
+
+@pytest.mark.parametrize("slices", [1, 4])
+@pytest.mark.parametrize("K", [1, 3, 6, 16])
+def test_candidate_counts(K, slices):
+    _check(wl.make_arm(seed=0, n_spheres=52), [30], [5], [9], [0], K, slices)
+
+
+@pytest.mark.parametrize("n_spheres", [1, 7, 23, 112])
+def test_spheres_per_link(n_spheres):
+    _check(wl.make_arm(seed=0, n_spheres=n_spheres), [40], [4], [8], [0], 4, 1)
+
+
+@pytest.mark.parametrize("slices", [1, 2, 4])
+def test_two_arms_crowded(slices):
+    """300 cuboids in the same space: every queue overflows many times."""
+    _check(wl.make_two_arm(seed=0, n_spheres=120), [300], [2], [5], [0], 4, slices)
+
+
+def test_many_unequal_problems():
+    """Two steps of the search for a workgroup's problem (more than 64)."""
+    rng = np.random.default_rng(24)
+    P = 150
+    _check(wl.make_arm(seed=0, n_spheres=20), [12, 0, 5], rng.integers(1, 6, P), rng.integers(1, 5, P),
+           rng.integers(0, 3, P), 3, 1)
