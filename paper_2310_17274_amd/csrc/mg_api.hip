@@ -747,6 +747,12 @@ StateSet state_set(mg_batch* b, float* x, int i) {
                   b->fs_meta};
 }
 
+// Per-seed sums of an evaluation's K candidates.
+mg::ReduceArgs reduce_args(const mg_batch* b, int K, float* cost, float* min_clear, float* gd) {
+  return mg::ReduceArgs{b->d_seed, b->uniform_T, b->max_n / b->ctx->D, b->n_seeds, b->rows, K,
+                        b->cost_e, b->mc_e, gd ? b->gd_e : nullptr, cost, min_clear, gd};
+}
+
 mg_status check_K_alpha(const mg_batch* b, int K, const float* alpha) {
   if (K < 1 || K > b->K_max) return fail(MG_ERR_SHAPE, "K = %d outside 1..%d", K, b->K_max);
   if (!alpha) return fail(MG_ERR_ARG, "alpha is null");
@@ -1136,8 +1142,7 @@ mg_status mg_cost_grad(mg_ctx* c, mg_batch* b, const float* q_start, const float
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = enqueue_eval(c, b, q_start, goal, q, nullptr, 1, nullptr, grad != nullptr, grad, nullptr, s)) != MG_OK)
     return st;
-  mg::ReduceArgs ra{b->d_seed, b->n_seeds, b->cost_e, b->mc_e, cost, min_clear};
-  HIP_TRY(mg::launch_reduce(ra, s));
+  HIP_TRY(mg::launch_reduce(reduce_args(b, 1, cost, min_clear, nullptr), s));
   return MG_OK;
 }
 
@@ -1173,17 +1178,10 @@ mg_status mg_linesearch_eval(mg_ctx* c, mg_batch* b, const float* q_start, const
   if ((st = check_K_alpha(b, K, alpha)) != MG_OK) return st;
   if (!q_start || !goal || !x || !dir || !cost || !gd) return fail(MG_ERR_ARG, "null argument");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // the launch mg_linesearch and mg_solve make for these K candidates
-  if ((st = enqueue_eval(c, b, q_start, goal, x, dir, K, alpha, true, nullptr, nullptr, s)) != MG_OK) return st;
-  const size_t R = b->rows;
-  for (int k = 0; k < K; ++k) {
-    mg::ReduceArgs rc{b->d_seed, b->n_seeds, b->cost_e + k * R, b->mc_e + k * R, cost + (size_t)k * b->n_seeds,
-                      min_clear ? min_clear + (size_t)k * b->n_seeds : nullptr};
-    HIP_TRY(mg::launch_reduce(rc, s));
-    mg::ReduceArgs rg{b->d_seed, b->n_seeds, b->gd_e + k * R, b->mc_e + k * R, gd + (size_t)k * b->n_seeds, nullptr};
-    HIP_TRY(mg::launch_reduce(rg, s));
-  }
-  if (grad) HIP_TRY(mg::launch_copy(b->grad_e, grad, (size_t)K * R * c->D, s));
+  // the launch mg_linesearch and mg_solve make for these K candidates, its
+  // gradients straight into the caller's array
+  if ((st = enqueue_eval(c, b, q_start, goal, x, dir, K, alpha, true, grad, nullptr, s)) != MG_OK) return st;
+  HIP_TRY(mg::launch_reduce(reduce_args(b, K, cost, min_clear, gd), s));
   return MG_OK;
 }
 
@@ -1664,8 +1662,7 @@ mg_status mg_solve(mg_ctx* c, mg_batch* b, const float* q_start, const float* go
 
   // initial cost and gradient, best = start, fresh history per seed
   if ((st = enqueue_eval(c, b, q_start, goal, x, nullptr, 1, nullptr, true, b->g_cur, nullptr, s)) != MG_OK) return st;
-  mg::ReduceArgs ra{b->d_seed, b->n_seeds, b->cost_e, b->mc_e, b->c_cur, nullptr};
-  HIP_TRY(mg::launch_reduce(ra, s));
+  HIP_TRY(mg::launch_reduce(reduce_args(b, 1, b->c_cur, nullptr, nullptr), s));
   HIP_TRY(mg::launch_copy(b->c_cur, b->best_c, b->n_seeds, s));
   HIP_TRY(mg::launch_copy(x, b->best_x, RD, s));
   HIP_TRY(mg::launch_fill_i32(b->first, 1, b->n_seeds, s));

@@ -251,11 +251,15 @@ struct SpeedAdjArgs {
 
 struct ReduceArgs {
   const SeedInfo* seeds;
-  int n_seeds;
-  const float* cost_e;     // [rows]
-  const float* mc_e;       // [rows]
-  float* cost;             // [seeds]
-  float* min_clear;        // [seeds] or null
+  int uniform_T;           // > 0: every seed has this horizon (seed s starts at row s T)
+  int max_T;               // longest horizon
+  int n_seeds, rows, K;
+  const float* cost_e;     // [K][rows]
+  const float* mc_e;       // [K][rows]
+  const float* gd_e;       // [K][rows] or null
+  float* cost;             // [K][seeds]
+  float* min_clear;        // [K][seeds] or null
+  float* gd;               // [K][seeds] (with gd_e)
 };
 
 struct SelectArgs {
