@@ -131,3 +131,28 @@ def test_plan_around_obstacles_is_valid():
     np.testing.assert_array_equal(path[0], pair[0].astype(np.float32))
     np.testing.assert_array_equal(path[-1], pair[1].astype(np.float32))
     assert _path_valid(r, boxes, path.astype(np.float64), res, robot)
+
+
+@pytest.mark.parametrize("n_max", [1, 62, 63, 64, 65, 130])
+def test_steer_sample_counts(n_max):
+    """Edges whose samples fill one wave exactly, fall one short or spill
+    over, against the reference's last valid sample (a mismatch only where
+    the deciding sample's clearance is within rounding of zero)."""
+    robot = wl.robot_f32(wl.make_arm(seed=0, n_spheres=20))
+    worlds = wl.worlds_f32(wl.make_worlds(2, [12]))
+    r = ref.Ref(robot)
+    rng = np.random.default_rng(71)
+    n, res = 24, 2.0 / n_max
+    a = F32(rng.uniform(-2.0, 2.0, (n, 7)))
+    b_ = F32(np.clip(a + rng.uniform(-1.9, 1.9, (n, 7)), -2.75, 2.75))
+    b_[0] = F32(a[0])                 # no length: one step
+    ctx, b = _ctx(robot, worlds, n, n_max)
+    _, last, _ = ctx.mg_steer(b, _dev(a), _dev(b_), res, n_max)
+    last = last.cpu().numpy()
+    for e in range(n):
+        h, _, _ = ref.steer(r, worlds.world(0), a[e], b_[e], float(np.float32(res)), robot.q_lo, robot.q_hi)
+        if last[e] != h:
+            steps = int(math.floor(np.abs(b_[e] - a[e]).max() / res)) + 1
+            q = a[e] + ((min(last[e], h) + 1) / steps) * (b_[e] - a[e])
+            _, _, mc = r.cost_grad_batch(worlds.world(0), np.zeros(7), np.array([[0, 0, 0, 1.0, 0, 0, 0]]), 1, q)
+            assert abs(float(np.ravel(mc)[0])) <= 1e-5, e
