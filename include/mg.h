@@ -317,12 +317,10 @@ mg_status mg_autotune(mg_ctx *ctx, mg_batch *batch, const float *q_start, const 
  *   mean, var DEVICE [rows][D] in/out (var per element, rad^2)
  *   eps       DEVICE [n_iters][n_particles][rows][D] standard normal draws
  *   costs_out DEVICE [n_iters][seeds][n_particles] particle costs, or NULL
- * The costing launch is wave per link (one slot group per wave, unless
- * mg_batch_set_layout chose two or four) when n_particles is the last reserved
- * count and the layout fits the robot, lane per link when
- * mg_batch_set_layout chose it (self-collision and the speed metric keep
- * wave per link); the autotuner's choice for line-search candidates is not
- * carried over.
+ * The costing launch is lane per link unless mg_batch_set_layout chose a
+ * wave-per-link layout or self-collision or the speed metric needs it (then
+ * with one slot group per wave, unless two or four were chosen, and
+ * n_particles the last reserved count).
  * MG_ERR_STATE if n_particles exceeds the reservation.  Capturable. */
 mg_status mg_batch_reserve_particles(mg_batch *batch, int n_particles);
 mg_status mg_particles(mg_ctx *ctx, mg_batch *batch, const float *q_start, const float *goal,
@@ -331,10 +329,10 @@ mg_status mg_particles(mg_ctx *ctx, mg_batch *batch, const float *q_start, const
 
 /* The particle stage with its noise drawn on the device: as mg_particles,
  * with round it's draws eps[k][row][j] the counter-based standard normals of
- * mg_philox_normals(seed, it, ...) (it = 0 .. n_iters - 1 <= 65535).  The
- * evaluation kernel makes each particle's draws where it forms the particle
- * and the update kernel makes them again (one Philox block per four
- * elements): no draw is stored, read back or uploaded.  Capturable. */
+ * mg_philox_normals(seed, it, ...) (it = 0 .. n_iters - 1 <= 65535).  Each
+ * round's draws are made once into the batch's workspace (up to 1 GiB, held
+ * from mg_batch_reserve_particles on); beyond that the kernels make them
+ * where they use them.  Capturable. */
 mg_status mg_particles_seeded(mg_ctx *ctx, mg_batch *batch, const float *q_start, const float *goal,
                               float *mean, float *var, int n_particles, int n_iters,
                               unsigned long long seed, float beta, float k_mu, float k_sigma,

@@ -73,6 +73,8 @@ void dev_free(T*& p) {
 constexpr int kNumSlices = 4;
 constexpr int kSlices[kNumSlices] = {1, 2, 4, 8};
 constexpr int kNumRowBlocks = 6;   // 1, 2, .. 32 rows
+// Largest workspace for a round of particle draws.
+constexpr size_t kMaxDrawBytes = (size_t)1 << 30;
 
 }  // namespace
 
@@ -167,6 +169,9 @@ struct mg_batch {
   float* p_cost = nullptr;
   int p_cap = 0;
   int pm_K = 0;
+  // one round's draws [p_cap][rows][D] (null beyond kMaxDrawBytes: the
+  // kernels then make the draws themselves)
+  float* p_draw = nullptr;
   mg::WlChunk* d_chunk_pm[3] = {};
   int chunks_pm[3] = {};
   // speed metric with gradients: per (candidate, row, sphere) terms of the
@@ -1063,7 +1068,7 @@ void mg_batch_destroy(mg_batch* b) {
   dev_free(b->cost_e); dev_free(b->gd_e); dev_free(b->mc_e); dev_free(b->grad_e); dev_free(b->pe_e);
   dev_free(b->c_cur); dev_free(b->g_cur); dev_free(b->dir); dev_free(b->best_c); dev_free(b->best_x);
   dev_free(b->first); dev_free(b->S); dev_free(b->Y); dev_free(b->x_prev); dev_free(b->g_prev);
-  dev_free(b->rho); dev_free(b->meta); dev_free(b->p_cost); dev_free(b->sel_dt);
+  dev_free(b->rho); dev_free(b->meta); dev_free(b->p_cost); dev_free(b->p_draw); dev_free(b->sel_dt);
   dev_free(b->sel_jerk);
   dev_free(b->fs_x); dev_free(b->fs_c); dev_free(b->fs_g); dev_free(b->fs_dir); dev_free(b->fs_meta);
   dev_free(b->fs_cost_e); dev_free(b->fs_gd_e); dev_free(b->fs_mc_e); dev_free(b->fs_grad_e);
@@ -1372,7 +1377,14 @@ mg_status mg_batch_reserve_particles(mg_batch* b, int n_particles) {
   if (n_particles > b->p_cap) {
     dev_free(b->p_cost);
     b->p_cap = 0;
+    dev_free(b->p_draw);
     if ((st = dev_alloc(&b->p_cost, (size_t)n_particles * b->rows)) != MG_OK) return st;
+    // (the draws' workspace is a convenience: without it the kernels draw)
+    const size_t draws = (size_t)n_particles * b->rows * b->ctx->D;
+    if (draws * sizeof(float) <= kMaxDrawBytes && dev_alloc(&b->p_draw, draws) != MG_OK) {
+      b->p_draw = nullptr;
+      (void)hipGetLastError();
+    }
     b->p_cap = n_particles;
   }
   // wave-per-link records for this particle count
@@ -1401,14 +1413,10 @@ mg_status particle_rounds(mg_ctx* c, mg_batch* b, const float* q_start, const fl
   if (!q_start || !goal || !mean || !var) return fail(MG_ERR_ARG, "null q_start, goal, mean or var");
   if (!(k_mu >= 0.0f && k_mu <= 1.0f) || !(k_sigma >= 0.0f && k_sigma <= 1.0f))
     return fail(MG_ERR_ARG, "k_mu and k_sigma must lie in [0, 1]");
-  // wave per link with one slot group (64 particles of one row per
-  // workgroup: their spheres lie close together, so the wave-level cuboid
-  // cull is tight) unless mg_batch_set_layout chose another layout; the
-  // autotuner's choice for line-search candidates is not carried over (on
-  // the two-arm tree with 500 cuboids and swept collision a particle round
-  // measured 139 ms with one slot group, 244 ms with two, 350 ms lane per
-  // link)
-  const bool lane_set = b->layout_set && b->layout == 0;
+  // lane per link unless mg_batch_set_layout chose a wave-per-link layout (or
+  // a term needs it): 32 seeds x 32 x 128 particles, 52 spheres, 40 cuboids
+  // measured 72 us a launch against 173 wave per link
+  const bool lane_set = !(b->layout_set && b->layout == 1);
   const int groups =
       b->layout_set && b->wl_groups > 1 && wl_groups_possible(c, b->wl_groups) ? b->wl_groups : 1;
   const int halves = groups > 1 ? 1 : (b->wl_halves > 0 ? b->wl_halves : (wl_halves_possible(c) ? 2 : 1));
@@ -1427,6 +1435,13 @@ mg_status particle_rounds(mg_ctx* c, mg_batch* b, const float* q_start, const fl
   const int hi = pick_slices(b, (long)b->rows * n_particles);
   for (int it = 0; it < n_iters; ++it) {
     const float* e = eps ? eps + (size_t)it * draws : nullptr;
+    // without draws from the caller, a round's are made once in the batch's
+    // workspace: the evaluation would make each of them for every row whose
+    // stencils it reaches (nine), the update once more
+    if (!e && b->p_draw) {
+      HIP_TRY(mg::launch_philox_normals(seed, it, 1, n_particles, (long long)b->rows * c->D, b->p_draw, s));
+      e = b->p_draw;
+    }
     mg::EvalArgs a = eval_args(c, b, hi, q_start, goal, mean, e, n_particles, nullptr);
     a.var = var;
     if (e) a.d_stride = (size_t)b->rows * c->D;
@@ -1452,6 +1467,7 @@ mg_status particle_rounds(mg_ctx* c, mg_batch* b, const float* q_start, const fl
     pa.rows = b->rows;
     pa.dof = c->D;
     pa.N = n_particles;
+    pa.max_n = b->max_n;
     pa.beta = beta;
     pa.k_mu = k_mu;
     pa.k_sigma = k_sigma;

@@ -327,6 +327,7 @@ struct SelFuse {
 struct ParticleArgs {
   const SeedInfo* seeds;
   int n_seeds, rows, dof, N;
+  int max_n;                   // largest T * D of a seed
   float beta, k_mu, k_sigma;   // beta <= 0: 0.1 x the seed's cost range
   const float* q_lo;
   const float* q_hi;
