@@ -610,76 +610,131 @@ hipError_t launch_steer_points(const SteerArgs& a, hipStream_t s) {
 // neighbour search, Alg.2).  Squared Euclidean distances summed joint by
 // joint in fp32 without fused multiply-add (each product and sum rounded, so
 // a host brute force in fp32 reproduces them bit for bit); ties go to the
-// lower node index.  One wave per query: each lane keeps the KMAX nearest of
-// its strided share of the nodes in a sorted register list, then k
-// wave-wide minimum rounds take the overall nearest in order, the owning
-// lane popping its head each round.
-template <int KMAX>
-__global__ __launch_bounds__(kWave) void knn_kernel(const KnnArgs a) {
+// lower node index.
+//
+// A wave holds QPW queries, their joint values in scalar registers, and
+// takes 64 nodes at a time, one per lane, from a tile that the workgroup's
+// four waves share in LDS.  Each query keeps ONE sorted list for the whole
+// wave, entry r in lane r, and its last distance as the bar a node has to
+// beat: about k (1 + ln(n / k)) of n nodes do, and each is put in place by a
+// ballot (its rank) and a shift by one lane.  (A list per lane met its bar
+// k (1 + ln(n / 64 k)) times in every lane, so that nearly every step of a
+// wave ran the insertion over KMAX registers.)  12000 x 12000 x 7, k = 11:
+// 672 us before, 157 now.  What bounds it is the arithmetic that the exact
+// sums need, three operations per joint and node (77 us of that), and the
+// insertions.
+constexpr int kKnnTile = kBlock;
+template <int D, int QPW>
+__global__ __launch_bounds__(kBlock) void knn_kernel(const KnnArgs a) {
 #pragma clang fp contract(off)
-  const int qi = blockIdx.x, lane = threadIdx.x, D = a.dof;
-  float q[kMaxDof];
+  constexpr int ST = D | 1;                        // (odd: a lane's node in its own banks)
+  __shared__ float s_n[kKnnTile * ST];
+  const int tid = threadIdx.x, lane = tid % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int q0 = ((int)blockIdx.x * (kBlock / kWave) + wave) * QPW;
+  float q[QPW][D], ld[QPW], bar[QPW];
+  int li[QPW];
 #pragma unroll
-  for (int j = 0; j < kMaxDof; ++j) q[j] = j < D ? a.queries[(size_t)qi * D + j] : 0.0f;
-  float bd[KMAX];
-  int bi[KMAX];
+  for (int u = 0; u < QPW; ++u) {
+    cfloat* src = (cfloat*)(a.queries) + (size_t)min(q0 + u, a.n_queries - 1) * D;
 #pragma unroll
-  for (int r = 0; r < KMAX; ++r) { bd[r] = INFINITY; bi[r] = INT_MAX; }
-  for (int i = lane; i < a.n_nodes; i += kWave) {
-    const float* nd = a.nodes + (size_t)i * D;
-    float d2 = 0.0f;
+    for (int j = 0; j < D; ++j) q[u][j] = src[j];
+    ld[u] = bar[u] = INFINITY;
+    li[u] = -1;
+  }
+  // (the next tile is read while this one is searched)
+  float pre[D];
+  auto read_tile = [&](int t0) {
+    const int nv = min(kKnnTile, a.n_nodes - t0) * D;
 #pragma unroll
-    for (int j = 0; j < kMaxDof; ++j)
-      if (j < D) {
-        const float u = nd[j] - q[j];
-        d2 = d2 + u * u;
-      }
-    if (d2 < bd[KMAX - 1]) {   // (a lane's indices increase: ties keep the earlier)
-      float cd = d2;
-      int ci = i;
+    for (int r = 0; r < D; ++r) pre[r] = a.nodes[(size_t)t0 * D + min(r * kBlock + tid, nv - 1)];
+  };
+  if (a.n_nodes > 0) read_tile(0);
+  for (int t0 = 0; t0 < a.n_nodes; t0 += kKnnTile) {
+    const int nt = min(kKnnTile, a.n_nodes - t0);
+    __syncthreads();
 #pragma unroll
-      for (int r = 0; r < KMAX; ++r) {
-        const bool sw = cd < bd[r];
-        const float td = bd[r];
-        const int ti = bi[r];
-        bd[r] = sw ? cd : td;
-        bi[r] = sw ? ci : ti;
-        cd = sw ? td : cd;
-        ci = sw ? ti : ci;
+    for (int r = 0; r < D; ++r) {
+      const int i = r * kBlock + tid;
+      s_n[(i / D) * ST + i % D] = pre[r];
+    }
+    __syncthreads();
+    if (t0 + kKnnTile < a.n_nodes) read_tile(t0 + kKnnTile);
+    for (int b = 0; b < nt; b += kWave) {
+      const int i = min(b + lane, nt - 1);
+      const bool in = b + lane < nt;
+      float nd[D];
+#pragma unroll
+      for (int j = 0; j < D; ++j) nd[j] = s_n[i * ST + j];
+#pragma unroll
+      for (int u = 0; u < QPW; ++u) {
+        float d2 = 0.0f;
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+          const float v = nd[j] - q[u][j];
+          d2 = d2 + v * v;
+        }
+        uint64_t hits = __ballot(in && d2 < bar[u]);
+        while (hits) {
+          // in index order, so an equal distance stays behind the earlier node
+          const int src = __builtin_ctzll(hits);
+          hits &= hits - 1;
+          const float cd = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d2), src));
+          if (!(cd < bar[u])) continue;
+          const int rank = __popcll(__ballot(ld[u] <= cd));
+          const float sd = dpp<0x138>(ld[u]);      // wave_shr:1
+          const int si = __builtin_amdgcn_update_dpp(0, li[u], 0x138, 0xF, 0xF, false);
+          ld[u] = lane > rank ? sd : lane == rank ? cd : ld[u];
+          li[u] = lane > rank ? si : lane == rank ? t0 + b + src : li[u];
+          bar[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ld[u]), a.k - 1));
+        }
       }
     }
   }
-  for (int r = 0; r < a.k; ++r) {
-    float md = bd[0];
-    int mi = bi[0];
 #pragma unroll
-    for (int o = kWave / 2; o >= 1; o >>= 1) {
-      const float od = __shfl_xor(md, o, kWave);
-      const int oi = __shfl_xor(mi, o, kWave);
-      const bool take = od < md || (od == md && oi < mi);
-      md = take ? od : md;
-      mi = take ? oi : mi;
+  for (int u = 0; u < QPW; ++u)
+    if (q0 + u < a.n_queries && lane < a.k) {
+      const size_t o = (size_t)(q0 + u) * a.k + lane;
+      a.idx[o] = li[u];
+      if (a.d2) a.d2[o] = ld[u];
     }
-    if (lane == 0) {
-      a.idx[(size_t)qi * a.k + r] = mi == INT_MAX ? -1 : mi;
-      if (a.d2) a.d2[(size_t)qi * a.k + r] = md;
-    }
-    if (bi[0] == mi && mi != INT_MAX) {   // the owner pops its head
-#pragma unroll
-      for (int u = 0; u + 1 < KMAX; ++u) { bd[u] = bd[u + 1]; bi[u] = bi[u + 1]; }
-      bd[KMAX - 1] = INFINITY;
-      bi[KMAX - 1] = INT_MAX;
-    }
-  }
+}
+
+template <int D>
+hipError_t launch_knn_d(const KnnArgs& a, hipStream_t s) {
+  // One query per wave while all of them are in flight at once (8192 waves:
+  // eight on each SIMD of 256 CUs); above that, two share every node that a
+  // wave reads (12000 nodes, k = 11, 7 joints: 10000 queries 129 us one by
+  // one, 123 by pairs; 14 joints 201 and 176; 12000 queries of 7 joints 157
+  // by pairs, 176 by fours).
+  constexpr int W = kBlock / kWave;
+  if (a.n_queries > 8192) knn_kernel<D, 2><<<(a.n_queries + 2 * W - 1) / (2 * W), kBlock, 0, s>>>(a);
+  else knn_kernel<D, 1><<<(a.n_queries + W - 1) / W, kBlock, 0, s>>>(a);
+  return hipGetLastError();
 }
 
 hipError_t launch_knn(const KnnArgs& a, hipStream_t s) {
   if (a.n_queries < 1) return hipSuccess;
   if (a.k < 1 || a.k > 32 || a.dof < 1 || a.dof > kMaxDof || a.n_nodes < 0) return hipErrorInvalidValue;
-  if (a.k <= 8) knn_kernel<8><<<a.n_queries, kWave, 0, s>>>(a);
-  else if (a.k <= 16) knn_kernel<16><<<a.n_queries, kWave, 0, s>>>(a);
-  else knn_kernel<32><<<a.n_queries, kWave, 0, s>>>(a);
-  return hipGetLastError();
+  static_assert(kMaxDof == 16, "one instantiation per joint count");
+  switch (a.dof) {
+    case 1: return launch_knn_d<1>(a, s);
+    case 2: return launch_knn_d<2>(a, s);
+    case 3: return launch_knn_d<3>(a, s);
+    case 4: return launch_knn_d<4>(a, s);
+    case 5: return launch_knn_d<5>(a, s);
+    case 6: return launch_knn_d<6>(a, s);
+    case 7: return launch_knn_d<7>(a, s);
+    case 8: return launch_knn_d<8>(a, s);
+    case 9: return launch_knn_d<9>(a, s);
+    case 10: return launch_knn_d<10>(a, s);
+    case 11: return launch_knn_d<11>(a, s);
+    case 12: return launch_knn_d<12>(a, s);
+    case 13: return launch_knn_d<13>(a, s);
+    case 14: return launch_knn_d<14>(a, s);
+    case 15: return launch_knn_d<15>(a, s);
+    default: return launch_knn_d<16>(a, s);
+  }
 }
 
 hipError_t launch_steer_scan(const SteerArgs& a, hipStream_t s) {

@@ -38,6 +38,22 @@ def test_knn_bit_exact_against_the_oracle(D, n, m, k):
     np.testing.assert_array_equal(d2.cpu().numpy(), rd)
 
 
+@pytest.mark.parametrize("D,n,m,k", [(1, 1, 1, 1), (2, 63, 3, 32), (7, 64, 4, 31), (5, 65, 5, 2), (16, 255, 1, 7),
+                                     (7, 256, 9, 11), (8, 257, 7, 32), (3, 513, 2, 17),
+                                     (7, 300, 8192, 11), (7, 300, 8193, 11), (4, 257, 8199, 32), (16, 70, 8194, 5)])
+def test_knn_tile_edges_and_queries_per_wave(D, n, m, k):
+    """Node counts around a wave (64) and a tile (256), query counts around a
+    workgroup and around the line (8192) where a wave takes two; coordinates
+    on a coarse lattice, so that most distances are shared by several nodes."""
+    rng = np.random.default_rng(n + m)
+    nodes = (rng.integers(-4, 5, (n, D)) / 4).astype(np.float32)
+    queries = (rng.integers(-4, 5, (m, D)) / 4).astype(np.float32)
+    idx, d2 = mg_knn(torch.as_tensor(nodes, device="cuda"), torch.as_tensor(queries, device="cuda"), k)
+    ri, rd = ref.knn(nodes, queries, k)
+    np.testing.assert_array_equal(idx.cpu().numpy(), ri)
+    np.testing.assert_array_equal(d2.cpu().numpy(), rd)
+
+
 def test_knn_fewer_nodes_than_k_and_no_nodes():
     rng = np.random.default_rng(7)
     nodes, queries = _knn_case(rng, 5, 20, 7)
