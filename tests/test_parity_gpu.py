@@ -633,6 +633,38 @@ def test_autograd_function_matches_adjoint():
     assert torch.allclose(q.grad, expect, rtol=1e-6, atol=0)
 
 
+@pytest.mark.parametrize("seeds,horizon", [([1], [1]), ([3], [5]), ([2, 1, 4], [7, 1, 3])])
+def test_autograd_scales_each_seed_by_its_own_gradient(seeds, horizon):
+    """Every row of the gradient carries its seed's incoming gradient: from a
+    strided and an expanded tensor, on another stream than the batch was made
+    on, and differentiably (the second derivative by that gradient is the
+    gradient's own row sums).  Products of two fp32 numbers: equal to one
+    rounding of each."""
+    from paper_2310_17274_amd.binding import MgCost
+    robot = wl.make_arm(seed=0, n_spheres=20)
+    batch = wl.make_batch(robot, 9, seeds, horizon, [0] * len(seeds))
+    case = Case(robot, wl.make_worlds(0, [6]), batch)
+    n, rows = sum(seeds), np.repeat(np.arange(sum(seeds)), np.repeat(horizon, seeds))
+    g = _dev(gpu_cost_grad(case)[1])
+    rows = torch.as_tensor(rows, device="cuda")
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        for w in (torch.linspace(0.5, 1.5, n, device="cuda"), torch.linspace(-1, 1, 2 * n, device="cuda")[::2],
+                  torch.full((1,), 0.75, device="cuda").expand(n)):
+            q = case.x.clone().requires_grad_(True)
+            w = w.detach().requires_grad_(True)
+            cost = MgCost.apply(q, case.ctx, case.b, case.q_start, case.goal)
+            gq, = torch.autograd.grad(cost, q, w, create_graph=True)
+            assert torch.equal(gq, g * w.detach()[rows].view(-1, 1))
+            gw, = torch.autograd.grad(gq.sum(), w)
+            want = torch.zeros(n, device="cuda", dtype=torch.float64).index_add(0, rows, g.double().sum(1))
+            scale = torch.zeros(n, device="cuda", dtype=torch.float64).index_add(0, rows, g.double().abs().sum(1))
+            # fp32 sums of at most 7 * 7 terms
+            assert ((gw.double() - want).abs() <= 49 * 6e-8 * scale).all()
+    torch.cuda.synchronize()
+
+
 def test_gpu_gradient_against_central_differences():
     """fp32 central differences of the GPU cost on a collision-free, smooth
     problem (no cuboid within reach), step 1e-3."""
