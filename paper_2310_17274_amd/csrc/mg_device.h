@@ -20,14 +20,23 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(4))) const v4i cv4i;
 typedef __attribute__((address_space(4))) const int cint;
 
+// log(cosh x).  Below 1 the even series x^2 / 2 + x^4 S(x^2), above it
+// |x| - ln 2 + log1p(exp(-2|x|)); S and (log1p(e) - e) / e^2 are Chebyshev fits
+// over their ranges (truncated below 3e-9 of the result).  Both sides cost
+// some 25 instructions; with sinhf, log1pf and expf they took 330, which the
+// few lanes at a trajectory's end made a whole wave wait for.  Largest error
+// over (0, 1000]: 1.4e-7 of the value (with those functions 2.7e-7).
 __device__ __forceinline__ float logcosh_f(float x) {
-  const float ax = fabsf(x);
-  if (ax < 1.0f) {
-    // log(cosh x) = log1p(2 sinh^2(x/2)): no cancellation for small x
-    const float s = sinhf(0.5f * ax);
-    return log1pf(2.0f * s * s);
-  }
-  return ax + log1pf(expf(-2.0f * ax)) - 0.693147180559945f;
+  const float ax = fabsf(x), t = ax * ax;
+  const float s =
+      fmaf(t, fmaf(t, fmaf(t, fmaf(t, fmaf(t, fmaf(t, -3.0158855e-5f, 1.9152599e-4f), -6.9956196e-4f), 2.1742769e-3f),
+                           -6.7440210e-3f), 2.2222102e-2f), -8.3333336e-2f);
+  const float near = t * fmaf(t, s, 0.5f);
+  const float e = __builtin_amdgcn_exp2f(-2.885390081777927f * ax);   // exp(-2 ax)
+  const float q =
+      fmaf(e, fmaf(e, fmaf(e, fmaf(e, -0.11962253f, 0.19334577f), -0.24954994f), 0.33331937f), -0.49999985f);
+  const float far = (ax - 0.693147180559945f) + fmaf(e * e, q, e);
+  return ax < 1.0f ? near : far;
 }
 
 // tanh(k r) / r with its limit k at r = 0.
@@ -154,25 +163,25 @@ __device__ __forceinline__ void identity(float* T) {
 }
 
 // Rotation matrix (row-major 3x3 inside a 3x4) -> unit quaternion wxyz,
-// Shepperd's method.
+// Shepperd's method; the four cases differ from lane to lane, so one root is
+// taken and the parts are selected.
 __device__ __forceinline__ void mat_to_quat(const float* T, float& qw, float& qx, float& qy, float& qz) {
   const float r00 = T[0], r01 = T[1], r02 = T[2];
   const float r10 = T[4], r11 = T[5], r12 = T[6];
   const float r20 = T[8], r21 = T[9], r22 = T[10];
   const float tr = r00 + r11 + r22;
-  if (tr >= r00 && tr >= r11 && tr >= r22) {
-    const float w = 0.5f * sqrtf(1.0f + tr), f = 0.25f * __builtin_amdgcn_rcpf(w);
-    qw = w; qx = (r21 - r12) * f; qy = (r02 - r20) * f; qz = (r10 - r01) * f;
-  } else if (r00 >= r11 && r00 >= r22) {
-    const float x = 0.5f * sqrtf(1.0f + r00 - r11 - r22), f = 0.25f * __builtin_amdgcn_rcpf(x);
-    qx = x; qw = (r21 - r12) * f; qy = (r01 + r10) * f; qz = (r02 + r20) * f;
-  } else if (r11 >= r22) {
-    const float y = 0.5f * sqrtf(1.0f - r00 + r11 - r22), f = 0.25f * __builtin_amdgcn_rcpf(y);
-    qy = y; qw = (r02 - r20) * f; qx = (r01 + r10) * f; qz = (r12 + r21) * f;
-  } else {
-    const float z = 0.5f * sqrtf(1.0f - r00 - r11 + r22), f = 0.25f * __builtin_amdgcn_rcpf(z);
-    qz = z; qw = (r10 - r01) * f; qx = (r02 + r20) * f; qy = (r12 + r21) * f;
-  }
+  const bool cw = tr >= r00 && tr >= r11 && tr >= r22, cx = !cw && r00 >= r11 && r00 >= r22, cy = !cw && !cx && r11 >= r22;
+  const float m = 0.5f * sqrtf(cw   ? 1.0f + tr
+                               : cx ? 1.0f + r00 - r11 - r22
+                               : cy ? 1.0f - r00 + r11 - r22
+                                    : 1.0f - r00 - r11 + r22);
+  const float f = 0.25f * __builtin_amdgcn_rcpf(m);
+  const float dx = (r21 - r12) * f, dy = (r02 - r20) * f, dz = (r10 - r01) * f;
+  const float sz = (r01 + r10) * f, sy = (r02 + r20) * f, sx = (r12 + r21) * f;
+  qw = cw ? m : cx ? dx : cy ? dy : dz;
+  qx = cw ? dx : cx ? m : cy ? sz : sy;
+  qy = cw ? dy : cx ? sz : cy ? m : sx;
+  qz = cw ? dz : cx ? sy : cy ? sx : m;
 }
 
 // Exact signed distance of a box-frame point p to a box with half extents h,
