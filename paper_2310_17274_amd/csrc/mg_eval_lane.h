@@ -78,35 +78,41 @@ __device__ __forceinline__ void link_pose(const float4& f0, const float4& f1, co
 // its lanes needs.  The pairs are therefore compacted in three steps, each
 // spreading its work over the wave's 64 lanes through queues in LDS:
 //   1. (link, cuboid) pairs, one per lane: the ball around the link's
-//      spheres over all the wave's evaluations against the cuboid;
-//   2. (evaluation, link, cuboid), one per lane: the evaluation's own ball;
-//   3. (evaluation, link, cuboid) items, one per lane (several lanes per item,
+//      spheres over a group of the wave's evaluations against the cuboid;
+//   2. (evaluation, link, cuboid), one per lane: the evaluation's own balls
+//      around the two parts of the link's spheres;
+//   3. (evaluation, part, cuboid) items, one per lane (several lanes per item,
 //      each with a share of the spheres, when few are left): the face test
-//      of every sphere of the link and, where it passes, the exact term.
-// With swept collision the exact term carries the trace and is long enough
-// to compact again: the spheres that pass the face test go through a second
-// queue, one (sphere, cuboid) pair per lane.
+//      of every sphere of the part and, where it passes, the exact term.
+// With swept collision the spheres whose trace may take a step (one in ten
+// of those that pass the face test, where segments are short) go through a
+// second queue, one (sphere, cuboid) pair and side per lane.  (Traced where
+// the exact term is, 64 lanes waited for the few that step: 6144 rows of two
+// arms among 500 cuboids, K = 4, took 579 us, 440 with the queue.)
 // The lanes' sums go back to the owners (evaluation, link) through an LDS
 // row per lane: each owner finds its rows from six ballots of the owners'
 // bits and adds them in lane order, so the results are deterministic.  (LDS
 // float atomics cost 194 cycles per wave instruction on gfx950, whatever the
 // addresses: eight of them per 64 pairs bounded this kernel, 411 us against
 // the figure below on 524288 inverse-kinematics evaluations.)
-// The culls are exact: the signed distance is 1-Lipschitz and max(|p| - h)
-// bounds it from below, so a pair they drop adds no cost and cannot lower the
-// clearance clamped at eta.
+// The culls are exact: the signed distance is 1-Lipschitz, so a ball whose
+// centre is further from a cuboid than its radius and eta holds no sphere that
+// matters (for spheres max(|p| - h), which bounds the distance from below,
+// does), and a pair they drop adds no cost and cannot lower the clearance
+// clamped at eta.
 //
 // Measured, us per launch (cost and gradient of every candidate), this layout
 // with its best number of copies against the best wave-per-link layout:
-//   524288 single configurations, 40 cuboids (4096 x 32 seeds, K = 4)  280 / 634
-//   64 problems, 84616 rows, 5 to 200 cuboids each, K = 4              163 / 250
-//   two arms, 120 spheres, 500 cuboids, swept, 6144 rows, K = 4        572 / 1101
-//   the same without the sweep                                         247 / 304
-//   128 seeds x 32, 40 cuboids, K = 8                                  17.0 / 28.7
-//   32 seeds x 32, 40 cuboids, K = 8                                   12.5 / 12.4
-//   4 seeds x 32, 10 cuboids, K = 4                                    8.3 / 12.4
-// A wave's time is now the kinematics and the joint terms (some 2100 cycles
-// each) and two memory rounds as much as the pairs.
+//   524288 single configurations, 40 cuboids (4096 x 32 seeds, K = 4)  216 / 634
+//   64 problems, 84616 rows, 5 to 200 cuboids each, K = 4              150 / 237
+//   two arms, 120 spheres, 500 cuboids, swept, 6144 rows, K = 4        387 / 1075
+//   the same without the sweep                                         183 / 294
+//   128 seeds x 32, 40 cuboids, K = 8                                  16.1 / 24.1
+//   32 seeds x 32, 40 cuboids, K = 8                                   11.1 / 11.6
+//   4 seeds x 32, 10 cuboids, K = 4                                    7.2 / 9.5
+// Large batches are bound by the vector instructions issued (some 280 per
+// evaluation, half of them kinematics, joint and pose terms, at one per four
+// cycles and SIMD), small ones by one wave's chain of them.
 
 // Compiler fence between LDS writes and reads of different lanes of one wave
 // (the hardware runs a wave's LDS instructions in order).
@@ -131,14 +137,22 @@ __device__ __forceinline__ float copies_op(float v, OP op) {
   if constexpr (H >= 8) v = op(v, lane_xor<4 * LPE>(v, lane));
   return v;
 }
-// Minimum over the evaluations of a wave: the lanes that differ in the bits
-// from STRIDE (the lanes of an evaluation) on.
-template <int STRIDE>
-__device__ __forceinline__ float evals_min(float v) {
-  if (STRIDE <= 8) v = fminf(v, dpp<0x128>(v));    // row_ror:8
-  if (STRIDE <= 16) v = swap16_min(v);
-  if (STRIDE <= 32) v = swap32_min(v);
-  return v;
+// Minimum of each of v[0..N) over GE (a power of two) neighbouring evaluations
+// of a wave, STRIDE lanes each.
+template <int STRIDE, int N>
+__device__ __forceinline__ void evals_min(float* v, int GE) {
+  if (STRIDE <= 8 && GE * STRIDE > 8) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = fminf(v[i], dpp<0x128>(v[i]));   // row_ror:8
+  }
+  if (STRIDE <= 16 && GE * STRIDE > 16) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = swap16_min(v[i]);
+  }
+  if (STRIDE <= 32 && GE * STRIDE > 32) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = swap32_min(v[i]);
+  }
 }
 __device__ __forceinline__ int lanes_below(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
@@ -146,12 +160,11 @@ __device__ __forceinline__ int lanes_below(uint64_t m) {
 
 constexpr int kLplWaves = kBlock / kWave;
 constexpr int kLplTile = 64;      // cuboids staged per tile
-constexpr int kLplNear = 3 * kWave;   // entries of the near-pair queue (two spheres are tested between checks)
+constexpr int kLplPairs = 4 * kWave;   // entries of the (group, link, cuboid) queue
+constexpr int kLplTrace = 5 * kWave / 2;   // entries of the trace queue (two spheres are tested between checks)
 // float4 between the rows of a staged tile (one more than the cuboids: the
 // four rows of a cuboid, read together, then lie in different banks)
 constexpr int kLplStride = kLplTile + 1;
-constexpr int kLplGroup = 4;      // cuboids tested between queue checks
-constexpr int kLplQueue = kWave - 1 + kLplGroup * kWave;   // entries a queue may hold
 
 // LDS of a lane-per-link workgroup, float offsets (kept a multiple of 4).
 // Shared: rows of x and of d (or the particle variance), limits and start,
@@ -159,6 +172,11 @@ constexpr int kLplQueue = kWave - 1 + kLplGroup * kWave;   // entries a queue ma
 // float4, in particle mode the draws; then per wave: link poses (and with
 // swept collision the neighbouring poses and the trace's reach), the
 // evaluations' and the links' balls, the lanes' sums, and the queues.
+// Most groups of evaluations a wave's links are bounded over.
+__host__ __device__ constexpr int lpl_groups(int lpe, int H) {
+  const int epw = kWave / (lpe * H);
+  return epw < 4 ? epw : 4;
+}
 struct LplLds {
   int x, d, lim, goal, etf, slot, box, eps, wave, wave_size, total;
 };
@@ -180,24 +198,25 @@ __host__ __device__ inline LplLds lpl_lds(int lpe, int H, int rb, int kb, int D,
   o.box = take(kLplStride * 16);
   o.eps = take(pm ? kb * rs * D : 0);
   o.wave = at;
-  o.wave_size = (sw ? 36 : 12) * ow + (sw ? (ow + 3) / 4 * 4 : 0) + 4 * ow + 4 * lpe + 8 * (kWave + 2) +
-                (sw ? kLplNear : 0) + (lpe * kLplTile + 2 * kWave) / 2;
+  o.wave_size = (sw ? 36 : 12) * ow + (sw ? (ow + 3) / 4 * 4 : 0) + 8 * ow + 4 * lpe * lpl_groups(lpe, H) + 8 * (kWave + 2) +
+                (sw ? kLplTrace / 2 : 0) + (kLplPairs + 3 * kWave) / 2;
   o.total = at + kLplWaves * o.wave_size;
   return o;
 }
 
 // One sphere against one cuboid in the box frame: cost, clearance and, with
 // GRAD, the box-frame force b (d cost / d centre) and its moment m about the
-// box origin, all accumulated.  ax.. = |p| - h, m3 their maximum.
+// box origin, all accumulated, and the distance sdf.  ax.. = |p| - h, m3 their
+// maximum.
 template <bool GRAD>
 __device__ __forceinline__ void pair_term(float px, float py, float pz, float ax, float ay, float az, float m3,
                                           float r, float w, float eta, float inv_eta, float& cost, float& mc,
-                                          float* b, float* m) {
+                                          float* b, float* m, float& sdf) {
   const float qx = fmaxf(ax, 0.0f), qy = fmaxf(ay, 0.0f), qz = fmaxf(az, 0.0f);
   const float n2 = qx * qx + qy * qy + qz * qz;
   const bool out = n2 > 0.0f;
   const float n = __builtin_amdgcn_sqrtf(n2);
-  const float sdf = out ? n : m3;
+  sdf = out ? n : m3;
   mc = fminf(mc, sdf - r);
   // Eq.(10): the slope u / eta clamped to [0, 1], the cost its integral
   const float u = r - sdf + eta;
@@ -318,13 +337,13 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
   float* s_eps = s_mem + o.eps;
   float* s_w = s_mem + o.wave + wave * o.wave_size;
   float4* s_T = reinterpret_cast<float4*>(s_w);                            // [3 or 9][OW]
-  float4* s_ball = s_T + (SW ? 9 : 3) * OW;                                // [OW]
-  float4* s_lball = s_ball + OW;                                           // [LPE]
-  float4* s_res = s_lball + LPE;                                           // [2][kWave + 2]
-  unsigned* s_nq = reinterpret_cast<unsigned*>(s_res + 2 * (kWave + 2));   // [kLplNear] (SW)
-  float* s_ext = reinterpret_cast<float*>(s_nq + (SW ? kLplNear : 0));     // [OW] (SW)
-  unsigned short* s_pq = reinterpret_cast<unsigned short*>(s_ext + (SW ? (OW + 3) / 4 * 4 : 0));   // [LPE kLplTile]
-  unsigned short* s_q = s_pq + LPE * kLplTile;                             // [2 kWave]
+  float4* s_ball = s_T + (SW ? 9 : 3) * OW;                                // [2][OW], by part
+  float4* s_lball = s_ball + 2 * OW;                                       // [groups][L]
+  float4* s_res = s_lball + LPE * lpl_groups(LPE, H);                                            // [2][kWave + 2]
+  unsigned short* s_tq = reinterpret_cast<unsigned short*>(s_res + 2 * (kWave + 2));   // [kLplTrace] (SW)
+  float* s_ext = reinterpret_cast<float*>(s_tq + (SW ? kLplTrace : 0));    // [OW] (SW)
+  unsigned short* s_pq = reinterpret_cast<unsigned short*>(s_ext + (SW ? (OW + 3) / 4 * 4 : 0));   // [kLplPairs]
+  unsigned short* s_q = s_pq + kLplPairs;                                  // [3 kWave]
 
   // ---- one round of loads: this lane's link tables, and the staging ----
   const int lj = l < L ? l : 0;
@@ -332,7 +351,8 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
   const float4 F0 = reinterpret_cast<const float4*>(a.rb.fixed_tf + lj * 12)[0];
   const float4 F1 = reinterpret_cast<const float4*>(a.rb.fixed_tf + lj * 12)[1];
   const float4 F2 = reinterpret_cast<const float4*>(a.rb.fixed_tf + lj * 12)[2];
-  const float4 bl = a.wl.ball[lj * kWlBalls];
+  const float4* bls = a.ln.sphere + LPE * maxs + 3 * l;
+  const float4 bl = bls[0], bl0 = bls[1], bl1 = bls[2];
   const int r_lo = max(row0, row0 + first - 4);
   const int r_hi = min(row0 + nrows - 1, row0 + first + RB - 1 + 4);
   const int n_st = (r_hi - r_lo + 1) * D;
@@ -420,8 +440,9 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
       // the cull's reach: half the longest segment over the link's spheres
       // (slightly widened so rounding never culls a sample the trace takes)
       float l2 = 0.0f;
-      for (int s = 0; s < info.z; ++s) {
+      for (int s = 0; s < maxs; ++s) {
         const float4 ls = s_slot[l * maxs + s];
+        if (ls.w <= -1e29f) continue;
         auto seg2 = [&](const float* N) {
           const float ux = (N[0] - Tm[0]) * ls.x + (N[1] - Tm[1]) * ls.y + (N[2] - Tm[2]) * ls.z + (N[3] - Tm[3]);
           const float uy = (N[4] - Tm[4]) * ls.x + (N[5] - Tm[5]) * ls.y + (N[6] - Tm[6]) * ls.z + (N[7] - Tm[7]);
@@ -455,19 +476,34 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
   const float cbx = Tm[0] * bl.x + Tm[1] * bl.y + Tm[2] * bl.z + Tm[3];
   const float cby = Tm[4] * bl.x + Tm[5] * bl.y + Tm[6] * bl.z + Tm[7];
   const float cbz = Tm[8] * bl.x + Tm[9] * bl.y + Tm[10] * bl.z + Tm[11];
-  const float rball = on && info.z > 0 ? (bl.w + eta) * 1.0001f + 1e-6f + ext : -1e30f;
-  if (sub == 0) s_ball[owner] = make_float4(cbx, cby, cbz, rball);
+  const float rball = (bl.w + eta) * 1.0001f + 1e-6f + ext;
+  if (H == 1 || sub < 2) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (H > 1 && h != sub) continue;             // (two copies: a part each)
+      const float4 q = h ? bl1 : bl0;
+      s_ball[h * OW + owner] = make_float4(Tm[0] * q.x + Tm[1] * q.y + Tm[2] * q.z + Tm[3],
+                                           Tm[4] * q.x + Tm[5] * q.y + Tm[6] * q.z + Tm[7],
+                                           Tm[8] * q.x + Tm[9] * q.y + Tm[10] * q.z + Tm[11],
+                                           (q.w + eta) * 1.0001f + 1e-6f + ext);
+    }
+  }
+  // the wave's evaluations in groups whose links lie near one another: the
+  // candidates of one row, and with trajectories neighbouring rows too (rows
+  // of one point each have nothing in common: over two rows of 4 candidates 78
+  // of 280 (link, cuboid) pairs passed the test below, by rows 11 of 560)
+  const int GE = T == 1 ? max(min(KB, EPW), EPW / lpl_groups(LPE, H)) : EPW, NG = EPW / GE;
   if (EPW > 1) {
-    // the link's ball over the wave's evaluations: centre of the bounding box
-    // of their centres, half its diagonal more (widened as above)
-    const float lx = evals_min<LPE * H>(cbx), ly = evals_min<LPE * H>(cby), lz = evals_min<LPE * H>(cbz);
-    const float ux = -evals_min<LPE * H>(-cbx), uy = -evals_min<LPE * H>(-cby), uz = -evals_min<LPE * H>(-cbz);
-    const float rm = -evals_min<LPE * H>(-rball);
-    const float hx = ux - lx, hy = uy - ly, hz = uz - lz;
-    if (lane < LPE)
-      s_lball[lane] = make_float4(0.5f * (lx + ux), 0.5f * (ly + uy), 0.5f * (lz + uz),
-                                  rm + 0.5f * sqrtf(hx * hx + hy * hy + hz * hz) * 1.0001f + 1e-6f);
-  } else if (lane < LPE) {
+    // the link's ball over a group: centre of the bounding box of the centres,
+    // half its diagonal more (widened as above)
+    float mn[7] = {cbx, cby, cbz, -cbx, -cby, -cbz, -rball};
+    evals_min<LPE * H, 7>(mn, GE);
+    const float hx = -mn[3] - mn[0], hy = -mn[4] - mn[1], hz = -mn[5] - mn[2];
+    if (l < L && sub == 0 && ew % GE == 0)
+      s_lball[ew / GE * L + l] =
+          make_float4(0.5f * (mn[0] - mn[3]), 0.5f * (mn[1] - mn[4]), 0.5f * (mn[2] - mn[5]),
+                      0.5f * sqrtf(hx * hx + hy * hy + hz * hz) * 1.0001f + 1e-6f - mn[6]);
+  } else if (lane < L) {
     s_lball[lane] = make_float4(cbx, cby, cbz, rball);
   }
   wave_lds_fence();
@@ -530,16 +566,19 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
     s_res[kWave + lane] = make_float4(0.0f, 3.0e38f, 0.0f, 0.0f);
     s_res[2 * kWave + 2 + lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   }
-  int nnq = 0;                                     // near pairs pending (SW)
-  // one (owner, sphere, cuboid) per lane: the exact term and the trace (SW)
-  auto near_chunk = [&](int base, int n) {
+  int ntq = 0;                                     // traces pending (SW)
+  // up to 32 (owner, sphere, cuboid), one per lane and side: the trace toward
+  // the previous waypoint in the lower half of the wave, the next in the upper
+  auto trace_chunk = [&](int base, int n) {
     if constexpr (SW) {
-      const bool act = lane < n;
-      const unsigned it = act ? s_nq[base + lane] : 0;
+      const int ii = lane & 31, side = 1 + (lane >> 5);
+      const bool act = ii < n;
+      const unsigned it = act ? s_tq[base + ii] : 0;
       const int ow = it & 63, ob = (it >> 6) & 63, sl = it >> 12;
       const float4 A0 = s_box[ob], A1 = s_box[kLplStride + ob], A2 = s_box[2 * kLplStride + ob],
                    Hh = s_box[3 * kLplStride + ob];
       const float4 t0 = s_T[ow], t1 = s_T[OW + ow], t2 = s_T[2 * OW + ow];
+      const float4 n0 = s_T[3 * side * OW + ow], n1 = s_T[(3 * side + 1) * OW + ow], n2 = s_T[(3 * side + 2) * OW + ow];
       const float4 ls = s_slot[(ow % LPE) * maxs + sl];
       const float cx = t0.x * ls.x + t0.y * ls.y + t0.z * ls.z + t0.w;
       const float cy = t1.x * ls.x + t1.y * ls.y + t1.z * ls.z + t1.w;
@@ -547,51 +586,40 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
       const float px = fmaf(A0.x, cx, fmaf(A0.y, cy, fmaf(A0.z, cz, A0.w)));
       const float py = fmaf(A1.x, cx, fmaf(A1.y, cy, fmaf(A1.z, cz, A1.w)));
       const float pz = fmaf(A2.x, cx, fmaf(A2.y, cy, fmaf(A2.z, cz, A2.w)));
-      const float ax = fabsf(px) - Hh.x, ay = fabsf(py) - Hh.y, az = fabsf(pz) - Hh.z;
-      float cost = 0.0f, b[3] = {0.0f, 0.0f, 0.0f}, gx, gy, gz, sdf;
-      if (GRAD) {
-        sdf = box_sdf(px, py, pz, ax, ay, az, gx, gy, gz);
-        dc_term_box(sdf, gx, gy, gz, ls.w, wc, eta, inv_eta, cost, b[0], b[1], b[2]);
-      } else {
-        sdf = box_dist(ax, ay, az);
-        dc_cost(sdf, ls.w, wc, eta, inv_eta, cost);
+      // the segment from the poses' difference, box frame
+      const float ux = (n0.x - t0.x) * ls.x + (n0.y - t0.y) * ls.y + (n0.z - t0.z) * ls.z + (n0.w - t0.w);
+      const float uy = (n1.x - t1.x) * ls.x + (n1.y - t1.y) * ls.y + (n1.z - t1.z) * ls.z + (n1.w - t1.w);
+      const float uz = (n2.x - t2.x) * ls.x + (n2.y - t2.y) * ls.y + (n2.z - t2.z) * ls.z + (n2.w - t2.w);
+      float cost = 0.0f, b[3] = {0.0f, 0.0f, 0.0f};
+      if (act)
+        trace_term<GRAD>(A0.x * ux + A0.y * uy + A0.z * uz, A1.x * ux + A1.y * uy + A1.z * uz,
+                         A2.x * ux + A2.y * uy + A2.z * uz, a.pr.sweep_steps, px, py, pz, Hh,
+                         box_dist(fabsf(px) - Hh.x, fabsf(py) - Hh.y, fabsf(pz) - Hh.z), ls.w, wc, eta, inv_eta, cost,
+                         b);
+      const bool some = cost != 0.0f;
+      if (__ballot(some)) {
+        const float fx = A0.x * b[0] + A1.x * b[1] + A2.x * b[2];
+        const float fy = A0.y * b[0] + A1.y * b[1] + A2.y * b[2];
+        const float fz = A0.z * b[0] + A1.z * b[1] + A2.z * b[2];
+        const float v[8] = {cost, 3.0e38f, fx, fy, fz, cy * fz - cz * fy, cz * fx - cx * fz, cx * fy - cy * fx};
+        deliver(some, ow, v);
       }
-      const float clr = sdf - ls.w;
-      if (act) {
-#pragma unroll
-        for (int side = 1; side < 3; ++side) {
-          // the segment from the neighbouring poses' difference, box frame
-          float u[3];
-#pragma unroll
-          for (int r = 0; r < 3; ++r) {
-            const float4 tc = r == 0 ? t0 : r == 1 ? t1 : t2, tn = s_T[(3 * side + r) * OW + ow];
-            u[r] = (tn.x - tc.x) * ls.x + (tn.y - tc.y) * ls.y + (tn.z - tc.z) * ls.z + (tn.w - tc.w);
-          }
-          trace_term<GRAD>(A0.x * u[0] + A0.y * u[1] + A0.z * u[2], A1.x * u[0] + A1.y * u[1] + A1.z * u[2],
-                           A2.x * u[0] + A2.y * u[1] + A2.z * u[2], a.pr.sweep_steps, px, py, pz, Hh, sdf, ls.w, wc,
-                           eta, inv_eta, cost, b);
-        }
-      }
-      const float fx = A0.x * b[0] + A1.x * b[1] + A2.x * b[2];
-      const float fy = A0.y * b[0] + A1.y * b[1] + A2.y * b[2];
-      const float fz = A0.z * b[0] + A1.z * b[1] + A2.z * b[2];
-      const float v[8] = {cost, clr, fx, fy, fz, cy * fz - cz * fy, cz * fx - cx * fz, cx * fy - cy * fx};
-      deliver(act, ow, v);
     }
   };
-  // n (owner, cuboid) items, one per lane, or 2, 4 or 8 lanes per item with
-  // a share of the link's spheres each
+  // n (owner, part, cuboid) items, one per lane, or 2, 4 or 8 lanes per item
+  // with a share of the part's spheres each
   auto link_chunk = [&](const unsigned short* q, int n) {
     const int sh = n > 32 ? 0 : n > 16 ? 1 : n > 8 ? 2 : 3, per = kWave >> sh;
     const int ii = lane & (per - 1);
     const bool act = ii < n;
     const unsigned it = act ? q[ii] : 0;
-    const int ow = it & 63, ob = it >> 6;
+    const int ow = it & 63, s_h = (it >> 6 & 1) * (maxs / 2), ob = it >> 7;
     const float4 A0 = s_box[ob], A1 = s_box[kLplStride + ob], A2 = s_box[2 * kLplStride + ob],
                  Hh = s_box[3 * kLplStride + ob];
     const float4 t0 = s_T[ow], t1 = s_T[OW + ow], t2 = s_T[2 * OW + ow];
-    const float4* sl = s_slot + (ow % LPE) * maxs;
-    const float reach = act ? eta + (SW ? s_ext[ow] : 0.0f) : -1e30f;
+    const float4* sl = s_slot + (ow % LPE) * maxs + s_h;
+    const float ext_o = SW ? s_ext[ow] : 0.0f;
+    const float reach = act ? eta + ext_o : -1e30f;
     const int s1 = lane >> (6 - sh);               // this lane's spheres: s1, s1 + (1 << sh), ..
     float cost = 0.0f, mc = 3.0e38f, b[3] = {0.0f, 0.0f, 0.0f}, m[3] = {0.0f, 0.0f, 0.0f};
     // (the face test; an unused slot's radius is -1e30: it never passes)
@@ -611,43 +639,47 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
       float4 la, lb;
       float pa[3], pb[3], ma, mb;
       const bool ha = test(sa, la, pa, ma), hb = test(sb, lb, pb, mb);
+      float da = 0.0f, db = 0.0f;
+      if (ha)
+        pair_term<GRAD>(pa[0], pa[1], pa[2], fabsf(pa[0]) - Hh.x, fabsf(pa[1]) - Hh.y, fabsf(pa[2]) - Hh.z, ma, la.w,
+                        wc, eta, inv_eta, cost, mc, b, m, da);
+      if (hb)
+        pair_term<GRAD>(pb[0], pb[1], pb[2], fabsf(pb[0]) - Hh.x, fabsf(pb[1]) - Hh.y, fabsf(pb[2]) - Hh.z, mb, lb.w,
+                        wc, eta, inv_eta, cost, mc, b, m, db);
       if constexpr (SW) {
-        const uint64_t ba = __ballot(ha), bb = __ballot(hb);
-        if (ha) s_nq[nnq + lanes_below(ba)] = it | sa << 12;
-        nnq += __popcll(ba);
-        if (hb) s_nq[nnq + lanes_below(bb)] = it | sb << 12;
-        nnq += __popcll(bb);
-        wave_lds_fence();
-        while (nnq >= kWave) {
-          nnq -= kWave;
-          near_chunk(nnq, kWave);
+        // the trace's first step, against half the link's longest segment
+        const float ra = la.w + eta, rb = lb.w + eta;
+        const bool wa = ha && (da < ra ? ra : da - ra) < ext_o, wb = hb && (db < rb ? rb : db - rb) < ext_o;
+        const uint64_t ba = __ballot(wa), bb = __ballot(wb);
+        if (wa) s_tq[ntq + lanes_below(ba)] = (unsigned short)(ow | ob << 6 | (s_h + sa) << 12);
+        ntq += __popcll(ba);
+        if (wb) s_tq[ntq + lanes_below(bb)] = (unsigned short)(ow | ob << 6 | (s_h + sb) << 12);
+        ntq += __popcll(bb);
+        if (ntq >= kWave / 2) {
+          wave_lds_fence();
+          while (ntq >= kWave / 2) {
+            ntq -= kWave / 2;
+            trace_chunk(ntq, kWave / 2);
+          }
         }
-      } else {
-        if (ha)
-          pair_term<GRAD>(pa[0], pa[1], pa[2], fabsf(pa[0]) - Hh.x, fabsf(pa[1]) - Hh.y, fabsf(pa[2]) - Hh.z, ma, la.w,
-                          wc, eta, inv_eta, cost, mc, b, m);
-        if (hb)
-          pair_term<GRAD>(pb[0], pb[1], pb[2], fabsf(pb[0]) - Hh.x, fabsf(pb[1]) - Hh.y, fabsf(pb[2]) - Hh.z, mb, lb.w,
-                          wc, eta, inv_eta, cost, mc, b, m);
       }
     }
-    if constexpr (!SW) {
-      // force and moment about the world origin (the box origin is at
-      // -A^T (A0.w, A1.w, A2.w)); items no sphere of which passed add nothing
-      const bool some = mc < 3.0e38f;
-      if (__ballot(some)) {
-        const float fx = A0.x * b[0] + A1.x * b[1] + A2.x * b[2];
-        const float fy = A0.y * b[0] + A1.y * b[1] + A2.y * b[2];
-        const float fz = A0.z * b[0] + A1.z * b[1] + A2.z * b[2];
-        const float ox = -(A0.x * A0.w + A1.x * A1.w + A2.x * A2.w);
-        const float oy = -(A0.y * A0.w + A1.y * A1.w + A2.y * A2.w);
-        const float oz = -(A0.z * A0.w + A1.z * A1.w + A2.z * A2.w);
-        const float v[8] = {cost, mc, fx, fy, fz,
-                            A0.x * m[0] + A1.x * m[1] + A2.x * m[2] + (oy * fz - oz * fy),
-                            A0.y * m[0] + A1.y * m[1] + A2.y * m[2] + (oz * fx - ox * fz),
-                            A0.z * m[0] + A1.z * m[1] + A2.z * m[2] + (ox * fy - oy * fx)};
-        deliver(some, ow, v);
-      }
+    // force and moment about the world origin (the box origin is at
+    // -A^T (A0.w, A1.w, A2.w)); items no sphere of which comes within r + eta
+    // add nothing
+    const bool some = mc < eta;
+    if (__ballot(some)) {
+      const float fx = A0.x * b[0] + A1.x * b[1] + A2.x * b[2];
+      const float fy = A0.y * b[0] + A1.y * b[1] + A2.y * b[2];
+      const float fz = A0.z * b[0] + A1.z * b[1] + A2.z * b[2];
+      const float ox = -(A0.x * A0.w + A1.x * A1.w + A2.x * A2.w);
+      const float oy = -(A0.y * A0.w + A1.y * A1.w + A2.y * A2.w);
+      const float oz = -(A0.z * A0.w + A1.z * A1.w + A2.z * A2.w);
+      const float v[8] = {cost, mc, fx, fy, fz,
+                          A0.x * m[0] + A1.x * m[1] + A2.x * m[2] + (oy * fz - oz * fy),
+                          A0.y * m[0] + A1.y * m[1] + A2.y * m[2] + (oz * fx - ox * fz),
+                          A0.z * m[0] + A1.z * m[1] + A2.z * m[2] + (ox * fy - oy * fx)};
+      deliver(some, ow, v);
     }
   };
 
@@ -659,56 +691,74 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
       __syncthreads();
     }
     const int nb = min(kLplTile, w1 - tl);
-    // the cuboid's distance bound from a ball's centre against its radius
-    auto reaches = [&](const float4& c4, int ob) -> bool {
-      const float4 A0 = s_box[ob], A1 = s_box[kLplStride + ob], A2 = s_box[2 * kLplStride + ob],
-                   Hh = s_box[3 * kLplStride + ob];
+    // the cuboid's distance from a ball's centre against its radius
+    auto reaches = [&](const float4& c4, const float4& A0, const float4& A1, const float4& A2, const float4& Hh,
+                       bool exact) -> bool {
       const float px = fmaf(A0.x, c4.x, fmaf(A0.y, c4.y, fmaf(A0.z, c4.z, A0.w)));
       const float py = fmaf(A1.x, c4.x, fmaf(A1.y, c4.y, fmaf(A1.z, c4.z, A1.w)));
       const float pz = fmaf(A2.x, c4.x, fmaf(A2.y, c4.y, fmaf(A2.z, c4.z, A2.w)));
-      return fmaxf(fabsf(px) - Hh.x, fmaxf(fabsf(py) - Hh.y, fabsf(pz) - Hh.z)) < c4.w;
+      const float ax = fabsf(px) - Hh.x, ay = fabsf(py) - Hh.y, az = fabsf(pz) - Hh.z;
+      const bool face = fmaxf(ax, fmaxf(ay, az)) < c4.w;
+      if (!exact) return face;
+      const float qx = fmaxf(ax, 0.0f), qy = fmaxf(ay, 0.0f), qz = fmaxf(az, 0.0f);
+      return face && fmaf(qx, qx, fmaf(qy, qy, qz * qz)) <= c4.w * c4.w;
     };
-    // 1. (link, cuboid) pairs i = l nb + o (the division by multiplication:
-    //    exact for i < 2^10, nb <= 64)
-    const int n_lo = L * nb;
-    const unsigned magic = ((1u << 20) + nb - 1) / nb;
-    int np = 0;
-#pragma unroll 2
-    for (int i0 = 0; i0 < n_lo; i0 += kWave) {
-      const int i = min(i0 + lane, n_lo - 1);
-      const int pl = (i * magic) >> 20, ob = i - pl * nb;
-      const bool hit = reaches(s_lball[pl], ob) && i0 + lane < n_lo;
-      const uint64_t bal = __ballot(hit);
-      if (hit) s_pq[np + lanes_below(bal)] = (unsigned short)(pl | ob << 6);
-      np += __popcll(bal);
-    }
-    wave_lds_fence();
-    // 2. (evaluation, link, cuboid), kWave / EPW pairs a step; then 3.
-    if constexpr (EPW == 1) {
-      for (int i = 0; i < np; i += kWave) link_chunk(s_pq + i, min(kWave, np - i));
-    } else {
-      constexpr int PPS = kWave / EPW;
-      int nq = 0;
-      for (int i0 = 0; i0 < np; i0 += PPS) {
-        const int pj = i0 + lane / EPW;
-        const unsigned it = s_pq[min(pj, np - 1)];
-        const int ow = (lane % EPW) * LPE + (it & 63), ob = it >> 6;
-        const bool hit = reaches(s_ball[ow], ob) && pj < np;
+    // 1. (group, link, cuboid) pairs i = (g L + l) nb + o, as many as the queue
+    //    holds at a time (the divisions by multiplication: exact for i < 2^13,
+    //    nb <= 64 and g L + l < 2^7, L <= 16); the face test alone (the
+    //    distance costs a third more here and spares less than that in 2.)
+    const int n_lo = NG * L * nb;
+    const unsigned magic = ((1u << 20) + nb - 1) / nb, magic_l = ((1u << 11) + L - 1) / L;
+    int nq = 0;
+    for (int i0 = 0; i0 < n_lo;) {
+      int np = 0;
+      for (; i0 < n_lo && np <= kLplPairs - kWave; i0 += kWave) {
+        const int i = min(i0 + lane, n_lo - 1);
+        const int gl = (i * magic) >> 20, ob = i - gl * nb;
+        const bool hit = reaches(s_lball[gl], s_box[ob], s_box[kLplStride + ob], s_box[2 * kLplStride + ob],
+                                 s_box[3 * kLplStride + ob], false) &&
+                         i0 + lane < n_lo;
         const uint64_t bal = __ballot(hit);
-        if (hit) s_q[nq + lanes_below(bal)] = (unsigned short)(ow | ob << 6);
-        nq += __popcll(bal);
-        wave_lds_fence();
-        const bool last = i0 + PPS >= np;
-        while (nq >= kWave || (last && nq > 0)) {
-          const int n = min(nq, kWave);
-          nq -= n;
-          link_chunk(s_q + nq, n);
+        const int g = EPW == 1 ? 0 : (gl * magic_l) >> 11;
+        if (hit) s_pq[np + lanes_below(bal)] = (unsigned short)((gl + g * (LPE - L)) | ob << 7);
+        np += __popcll(bal);
+      }
+      wave_lds_fence();
+      // 2. (evaluation, link, cuboid), kWave / GE pairs a step, both parts of
+      //    the link; then 3.
+      const int sh = __builtin_ctz(GE), step = kWave >> sh;
+      for (int j0 = 0; j0 < np; j0 += step) {
+        const int pj = j0 + (lane >> sh);
+        const unsigned it = s_pq[min(pj, np - 1)];
+        // (queued as g LPE + l: evaluation g GE + lane % GE)
+        const unsigned gl = it & 127, g = gl / LPE;
+        const int ow = (g * GE + (lane & (GE - 1))) * LPE + gl % LPE, ob = it >> 7;
+        const float4 A0 = s_box[ob], A1 = s_box[kLplStride + ob], A2 = s_box[2 * kLplStride + ob],
+                     Hh = s_box[3 * kLplStride + ob];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const bool hit = reaches(s_ball[h * OW + ow], A0, A1, A2, Hh, true) && pj < np;
+          const uint64_t bal = __ballot(hit);
+          if (hit) s_q[nq + lanes_below(bal)] = (unsigned short)(ow | h << 6 | ob << 7);
+          nq += __popcll(bal);
+        }
+        if (nq >= kWave) {
+          wave_lds_fence();
+          while (nq >= kWave) {
+            nq -= kWave;
+            link_chunk(s_q + nq, kWave);
+          }
         }
       }
     }
-    if (SW && nnq > 0) {                           // (the next tile replaces the cuboids)
-      near_chunk(0, nnq);
-      nnq = 0;
+    if (nq > 0) {
+      wave_lds_fence();
+      link_chunk(s_q, nq);
+    }
+    if (SW && ntq > 0) {                           // (the next tile replaces the cuboids)
+      wave_lds_fence();
+      trace_chunk(0, ntq);
+      ntq = 0;
     }
   }
 

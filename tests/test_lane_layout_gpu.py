@@ -15,10 +15,10 @@ from tests.test_parity_gpu import Case, _dev
 pytestmark = pytest.mark.gpu
 
 
-def _check(robot, counts, seeds, horizon, world, K, slices):
+def _check(robot, counts, seeds, horizon, world, K, slices, params=None):
     worlds = wl.make_worlds(21, counts)
     batch = wl.make_batch(robot, 22, seeds, horizon, world, noise=0.1)
-    case = Case(robot, worlds, batch, layout=(0, slices))
+    case = Case(robot, worlds, batch, params=params, layout=(0, slices))
     alpha = [float(a) for a in np.linspace(0.05, 1.0, K)]
     d = _direction(case, 0.1, 23)
     outs = []
@@ -54,6 +54,23 @@ def test_spheres_per_link(n_spheres):
 def test_two_arms_crowded(slices):
     """300 cuboids in the same space: every queue overflows many times."""
     _check(wl.make_two_arm(seed=0, n_spheres=120), [300], [2], [5], [0], 4, slices)
+
+
+@pytest.mark.parametrize("slices", [0, 1, 2, 4])
+@pytest.mark.parametrize("K", [1, 2, 4, 8])
+def test_rows_of_one_point(K, slices):
+    """Unrelated configurations side by side: links bounded per row, in one to
+    four groups a wave, with more pairs than their queue holds (70 cuboids)."""
+    _check(wl.make_arm(seed=0, n_spheres=52), [70], [37], [1], [0], K, slices)
+
+
+@pytest.mark.parametrize("slices", [1, 2, 4])
+@pytest.mark.parametrize("arms,horizon", [(1, 1), (1, 2), (1, 9), (2, 1), (2, 5)])
+def test_swept_traces(arms, horizon, slices):
+    """Continuous checking: no neighbour, one, two; segments long enough (noise
+    of 0.1 rad a joint) that many traces step."""
+    robot = wl.make_arm(seed=0, n_spheres=23) if arms == 1 else wl.make_two_arm(seed=0, n_spheres=50)
+    _check(robot, [12], [5], [horizon], [0], 4, slices, params=dict(swept=1))
 
 
 def test_many_unequal_problems():
