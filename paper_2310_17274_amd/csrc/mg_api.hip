@@ -811,6 +811,14 @@ bool fuse_ok(const mg_ctx* c, const mg_batch* b, int K, int m, const float* x) {
   const int halves = groups > 1 ? 1 : (b->wl_halves > 0 ? b->wl_halves : (wl_halves_possible(c) ? 2 : 1));
   if (halves != 1 || c->L + 1 > 8 || c->maxs / groups > 8) return false;
   const int T = b->uniform_T, E = mg::kWave / groups, n = T * c->D;
+  // A workgroup's own choice delays its evaluation, which pays while all of
+  // them are in flight at once: one to a CU (two of few candidates and slot
+  // groups).  us per iteration folded and apart, 7 joints x 32: 32 seeds, K = 8
+  // 14.2 / 15.9 (256 workgroups of two groups) but 23.4 / 17.8 (512 of four);
+  // 128 seeds, K = 8 30.2 / 29.4 (512), 46.4 / 27.9 (1024); 128 seeds, K = 4
+  // 17.4 / 20.3 (512 of two groups), 27.9 / 25.9 (1024).  A layout fixed by
+  // the caller folds at every size.
+  if (!b->layout_set && (long)b->rows * K / E > (K <= 4 && groups > 1 ? 512 : 256)) return false;
   return T > 0 && n > 2 * mg::kWave && n <= 4 * mg::kWave && n % 4 == 0 && K <= 8 && E % K == 0 && T % (E / K) == 0 && m >= 1 &&
          m <= 4 && ((uintptr_t)x & 15) == 0;
 }
@@ -1335,9 +1343,9 @@ mg_status mg_autotune(mg_ctx* c, mg_batch* b, const float* q_start, const float*
       b->wl_groups = 1;
       return st;
     }
-    // a layout in which the solve folds its choice in saves a launch of about
-    // 4 us per iteration (5.2 us and its gap, against 2.5 us folded in)
-    if (opts[o].layout == 1 && fuse_ok(c, b, K, std::min(4, b->m_max), nullptr)) us -= 4.0f;
+    // a layout in which the solve folds its choice in saves about 3 us per
+    // iteration (some 5 us for the choice's launch, against 2 to 2.6 folded in)
+    if (opts[o].layout == 1 && fuse_ok(c, b, K, std::min(4, b->m_max), nullptr)) us -= 3.0f;
     if (us < best_us) { best_us = us; best = o; }
   }
   b->layout = opts[best].layout;
@@ -1754,9 +1762,7 @@ mg_status mg_solve(mg_ctx* c, mg_batch* b, const float* q_start, const float* go
   // initial cost and gradient, best = start, fresh history per seed
   if ((st = enqueue_eval(c, b, q_start, goal, x, nullptr, 1, nullptr, true, b->g_cur, nullptr, s)) != MG_OK) return st;
   HIP_TRY(mg::launch_reduce(reduce_args(b, 1, b->c_cur, nullptr, nullptr), s));
-  HIP_TRY(mg::launch_copy(b->c_cur, b->best_c, b->n_seeds, s));
-  HIP_TRY(mg::launch_copy(x, b->best_x, RD, s));
-  HIP_TRY(mg::launch_fill_i32(b->first, 1, b->n_seeds, s));
+  HIP_TRY(mg::launch_copy2(x, b->best_x, RD, b->c_cur, b->best_c, b->n_seeds, s));
   if ((st = enqueue_lbfgs(c, b, m, 1, x, b->g_cur, b->dir, b->first, s)) != MG_OK) return st;
 
   if (fuse_ok(c, b, K, m, x)) {
@@ -1797,8 +1803,7 @@ mg_status mg_solve(mg_ctx* c, mg_batch* b, const float* q_start, const float* go
   for (; done < iters; ++done)
     if ((st = enqueue_iteration(c, b, q_start, goal, x, m, K, alpha, mode, s)) != MG_OK) return st;
 
-  HIP_TRY(mg::launch_copy(b->best_x, x, RD, s));
-  HIP_TRY(mg::launch_copy(b->best_c, best_cost, b->n_seeds, s));
+  HIP_TRY(mg::launch_copy2(b->best_x, x, RD, b->best_c, best_cost, b->n_seeds, s));
   if (best_seed || success) {
     if (success)
       if ((st = enqueue_eval(c, b, q_start, goal, x, nullptr, 1, nullptr, false, nullptr, b->pe_e, s)) != MG_OK)

@@ -474,7 +474,7 @@ hipError_t launch_knn(const KnnArgs& a, hipStream_t s);
 hipError_t launch_final(const FinalArgs& a, hipStream_t s);
 hipError_t launch_ee_pose(const EePoseArgs& a, hipStream_t s);
 hipError_t launch_boxes(const float* pose, const float* dims, int n, Box* out, hipStream_t s);
-hipError_t launch_copy(const float* src, float* dst, size_t n, hipStream_t s);
-hipError_t launch_fill_i32(int* dst, int v, size_t n, hipStream_t s);
+hipError_t launch_copy2(const float* src, float* dst, size_t n, const float* src2, float* dst2, size_t n2,
+                        hipStream_t s);
 
 }  // namespace mg

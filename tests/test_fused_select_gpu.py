@@ -127,3 +127,33 @@ def test_fused_solve_repeated_calls():
     b1 = _solve(case, False, True, 60, alpha)
     _same(a1, b1)
     _same(a2, b1)
+
+
+def test_tuned_batches_fold_while_their_workgroups_are_in_flight():
+    """Autotuned batches of 4 and 512 seeds: folded or not, the solve's bits
+    are those of the separate launches."""
+    from tests.test_parity_gpu import Case
+    robot = wl.make_arm(seed=0, n_spheres=52)
+    alpha = list(wl.cfg_cost_adjoint()[3]["alpha"])
+    for seeds in (4, 512):
+        case = Case(robot, wl.make_worlds(8, [10]), wl.make_batch(robot, 77, [seeds], [32], [0]))
+        d = torch.zeros_like(case.x)
+        case.ctx.mg_autotune(case.b, case.q_start, case.goal, case.x, d, alpha, launches=2)
+        _same(_solve(case, True, True, 12, alpha), _solve(case, False, True, 12, alpha))
+    assert not case.ctx.mg_solve_fuses(case.b, len(alpha), 4, case.x)
+
+
+@pytest.mark.parametrize("seeds", [1, 63, 64, 65, 130])
+def test_best_seed_is_the_first_of_the_lowest(seeds):
+    """Seeds that repeat: the first of equal costs wins at every count around
+    a wave."""
+    from tests.test_parity_gpu import Case
+    robot = wl.make_arm(seed=0, n_spheres=20)
+    batch = wl.make_batch(robot, 5, [seeds, 2], [3, 3], [0, 0])
+    case = Case(robot, wl.make_worlds(8, [4]), batch)
+    x = case.x.view(-1, 3, 7).clone()
+    x[:seeds] = x[(torch.arange(seeds, device="cuda") % 5)]
+    _, best, best_seed, _ = case.ctx.mg_solve(case.b, case.q_start, case.goal, x.view(-1, 7), 0, 4, [1.0],
+                                              graph_inner=1)
+    c = best.cpu().numpy()
+    assert best_seed.cpu().tolist() == [int(np.argmin(c[:seeds])), int(np.argmin(c[seeds:]))]
