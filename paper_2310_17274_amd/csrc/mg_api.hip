@@ -166,6 +166,7 @@ struct mg_batch {
   int wl_slices_max = 1;    // largest the scratch below holds
   float* wl_part = nullptr; // [chunks][slices][3 + D][64]
   int* wl_count = nullptr;  // [chunks], zero between launches
+  int* sum_count = nullptr; // [seeds][K_max], zero between launches (SeedSums)
   // particle stage: per-row costs of every particle [p_cap][rows], and
   // wave-per-link chunk records for pm_K particles per row
   float* p_cost = nullptr;
@@ -678,9 +679,16 @@ struct EvalOut {
   float *cost_e, *gd_e, *mc_e, *grad_e;
 };
 
+// Per-seed sums of an evaluation's K candidates.
+mg::ReduceArgs reduce_args(const mg_batch* b, int K, float* cost, float* min_clear, float* gd) {
+  return mg::ReduceArgs{b->d_seed, b->uniform_T, b->max_n / b->ctx->D, b->n_seeds, b->rows, K,
+                        b->cost_e, b->mc_e, gd ? b->gd_e : nullptr, cost, min_clear, gd};
+}
+
 mg_status enqueue_eval(mg_ctx* c, mg_batch* b, const float* q_start, const float* goal,
                        const float* x, const float* d, int K, const float* alpha, bool grad,
-                       float* grad_out, float* pe_out, hipStream_t s, const EvalOut* eo = nullptr) {
+                       float* grad_out, float* pe_out, hipStream_t s, const EvalOut* eo = nullptr,
+                       const mg::SeedSums* sums = nullptr) {
   if (needs_wl(c) && !use_wl(b, K))
     return fail(MG_ERR_UNSUPPORTED, "self-collision and the speed metric need the wave-per-link layout (at most 15 links)");
   const int hi = pick_slices(b, (long)b->rows * K);
@@ -693,6 +701,25 @@ mg_status enqueue_eval(mg_ctx* c, mg_batch* b, const float* q_start, const float
     a.grad_e = eo->grad_e;
   }
   a.pe_e = pe_out;
+  bool summed = false;
+  if (sums && !c->params.speed) {
+    if (b->uniform_T == 1) {
+      // one row per seed: the rows are the sums
+      a.cost_e = sums->cost;
+      if (sums->min_clear) a.mc_e = sums->min_clear;
+      if (sums->gd) a.gd_e = sums->gd;
+      summed = true;
+    } else if (!use_wl(b, K) && (long)b->rows * K <= 24576) {
+      // Made by the evaluation launch: a launch less, against the wait for
+      // the rows' stores at the end of every workgroup.  us per call with and
+      // without: 4 seeds x 32 12.3 / 14.8; 32 x 32, K = 8 15.1 / 17.9; 768 x 32
+      // (24576) 13.2 / 16.0; 1024 x 32 18.0 / 15.6; 512 x 32, K = 8 53 / 46.
+      a.sum = *sums;
+      a.sum.count = b->sum_count;
+      a.sum.n_seeds = b->n_seeds;
+      summed = true;
+    }
+  }
   const int slot = b->ev_next;
   // events are recorded around direct launches only (an event recorded while
   // a stream is captured is a graph dependency, not a timestamp)
@@ -738,6 +765,7 @@ mg_status enqueue_eval(mg_ctx* c, mg_batch* b, const float* q_start, const float
     sa.gd_e = a.gd_e;
     HIP_TRY(mg::launch_speed_adjoint(sa, s));
   }
+  if (sums && !summed) HIP_TRY(mg::launch_reduce(reduce_args(b, K, sums->cost, sums->min_clear, sums->gd), s));
   return MG_OK;
 }
 
@@ -833,12 +861,6 @@ StateSet state_set(mg_batch* b, float* x, int i) {
   if (i == 0) return StateSet{x, b->c_cur, b->g_cur, b->dir, b->cost_e, b->gd_e, b->mc_e, b->grad_e, b->meta};
   return StateSet{b->fs_x, b->fs_c, b->fs_g, b->fs_dir, b->fs_cost_e, b->fs_gd_e, b->fs_mc_e, b->fs_grad_e,
                   b->fs_meta};
-}
-
-// Per-seed sums of an evaluation's K candidates.
-mg::ReduceArgs reduce_args(const mg_batch* b, int K, float* cost, float* min_clear, float* gd) {
-  return mg::ReduceArgs{b->d_seed, b->uniform_T, b->max_n / b->ctx->D, b->n_seeds, b->rows, K,
-                        b->cost_e, b->mc_e, gd ? b->gd_e : nullptr, cost, min_clear, gd};
 }
 
 mg_status check_K_alpha(const mg_batch* b, int K, const float* alpha) {
@@ -1111,7 +1133,7 @@ mg_status mg_batch_create(mg_ctx* c, int P, const int* seeds, const int* horizon
       (st = dev_alloc(&b->pe_e, 2 * R)) != MG_OK || (st = dev_alloc(&b->c_cur, n_seeds)) != MG_OK ||
       (st = dev_alloc(&b->g_cur, RD)) != MG_OK || (st = dev_alloc(&b->dir, RD)) != MG_OK ||
       (st = dev_alloc(&b->best_c, n_seeds)) != MG_OK || (st = dev_alloc(&b->best_x, RD)) != MG_OK ||
-      (st = dev_alloc(&b->first, n_seeds)) != MG_OK || (st = dev_alloc(&b->S, mm * RD)) != MG_OK ||
+      (st = dev_alloc(&b->first, n_seeds)) != MG_OK || (st = dev_alloc(&b->sum_count, (size_t)n_seeds * K_max)) != MG_OK || (st = dev_alloc(&b->S, mm * RD)) != MG_OK ||
       (st = dev_alloc(&b->Y, mm * RD)) != MG_OK || (st = dev_alloc(&b->x_prev, RD)) != MG_OK ||
       (st = dev_alloc(&b->g_prev, RD)) != MG_OK || (st = dev_alloc(&b->rho, n_seeds * mm)) != MG_OK ||
       (st = dev_alloc(&b->meta, 2 * n_seeds)) != MG_OK || (st = dev_alloc(&b->sel_dt, n_seeds)) != MG_OK ||
@@ -1127,6 +1149,7 @@ mg_status mg_batch_create(mg_ctx* c, int P, const int* seeds, const int* horizon
   // zero the history metadata so a first step without reset is well defined
   if (hipMemset(b->meta, 0, 2 * n_seeds * sizeof(int)) != hipSuccess ||
       hipMemset(b->first, 0, n_seeds * sizeof(int)) != hipSuccess ||
+      hipMemset(b->sum_count, 0, (size_t)n_seeds * K_max * sizeof(int)) != hipSuccess ||
       hipDeviceSynchronize() != hipSuccess)
     return bail(fail(MG_ERR_HIP, "initialising batch workspaces failed"));
   *out = b;
@@ -1150,7 +1173,7 @@ void mg_batch_destroy(mg_batch* b) {
   for (auto& p : b->d_chunk_pm) dev_free(p);
   dev_free(b->cost_e); dev_free(b->gd_e); dev_free(b->mc_e); dev_free(b->grad_e); dev_free(b->pe_e);
   dev_free(b->c_cur); dev_free(b->g_cur); dev_free(b->dir); dev_free(b->best_c); dev_free(b->best_x);
-  dev_free(b->first); dev_free(b->S); dev_free(b->Y); dev_free(b->x_prev); dev_free(b->g_prev);
+  dev_free(b->first); dev_free(b->sum_count); dev_free(b->S); dev_free(b->Y); dev_free(b->x_prev); dev_free(b->g_prev);
   dev_free(b->rho); dev_free(b->meta); dev_free(b->p_cost); dev_free(b->p_draw); dev_free(b->sel_dt);
   dev_free(b->sel_jerk);
   dev_free(b->fs_x); dev_free(b->fs_c); dev_free(b->fs_g); dev_free(b->fs_dir); dev_free(b->fs_meta);
@@ -1228,10 +1251,8 @@ mg_status mg_cost_grad(mg_ctx* c, mg_batch* b, const float* q_start, const float
   if (st != MG_OK) return st;
   if (!q_start || !goal || !q || !cost) return fail(MG_ERR_ARG, "null q_start, goal, q or cost");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if ((st = enqueue_eval(c, b, q_start, goal, q, nullptr, 1, nullptr, grad != nullptr, grad, nullptr, s)) != MG_OK)
-    return st;
-  HIP_TRY(mg::launch_reduce(reduce_args(b, 1, cost, min_clear, nullptr), s));
-  return MG_OK;
+  const mg::SeedSums sums{cost, min_clear, nullptr, nullptr, 0};
+  return enqueue_eval(c, b, q_start, goal, q, nullptr, 1, nullptr, grad != nullptr, grad, nullptr, s, nullptr, &sums);
 }
 
 mg_status mg_lbfgs_step(mg_ctx* c, mg_batch* b, int m, int reset, const float* x, const float* g,
@@ -1268,9 +1289,8 @@ mg_status mg_linesearch_eval(mg_ctx* c, mg_batch* b, const float* q_start, const
   hipStream_t s = static_cast<hipStream_t>(stream);
   // the launch mg_linesearch and mg_solve make for these K candidates, its
   // gradients straight into the caller's array
-  if ((st = enqueue_eval(c, b, q_start, goal, x, dir, K, alpha, true, grad, nullptr, s)) != MG_OK) return st;
-  HIP_TRY(mg::launch_reduce(reduce_args(b, K, cost, min_clear, gd), s));
-  return MG_OK;
+  const mg::SeedSums sums{cost, min_clear, gd, nullptr, 0};
+  return enqueue_eval(c, b, q_start, goal, x, dir, K, alpha, true, grad, nullptr, s, nullptr, &sums);
 }
 
 mg_status mg_linesearch_noalloc(mg_ctx* c, mg_batch* b, const float* q_start, const float* goal,
@@ -1760,8 +1780,10 @@ mg_status mg_solve(mg_ctx* c, mg_batch* b, const float* q_start, const float* go
   const size_t RD = (size_t)b->rows * c->D;
 
   // initial cost and gradient, best = start, fresh history per seed
-  if ((st = enqueue_eval(c, b, q_start, goal, x, nullptr, 1, nullptr, true, b->g_cur, nullptr, s)) != MG_OK) return st;
-  HIP_TRY(mg::launch_reduce(reduce_args(b, 1, b->c_cur, nullptr, nullptr), s));
+  const mg::SeedSums sums{b->c_cur, nullptr, nullptr, nullptr, 0};
+  if ((st = enqueue_eval(c, b, q_start, goal, x, nullptr, 1, nullptr, true, b->g_cur, nullptr, s, nullptr, &sums)) !=
+      MG_OK)
+    return st;
   HIP_TRY(mg::launch_copy2(x, b->best_x, RD, b->c_cur, b->best_c, b->n_seeds, s));
   if ((st = enqueue_lbfgs(c, b, m, 1, x, b->g_cur, b->dir, b->first, s)) != MG_OK) return st;
 

@@ -154,6 +154,14 @@ __device__ __forceinline__ void evals_min(float* v, int GE) {
     for (int i = 0; i < N; ++i) v[i] = swap32_min(v[i]);
   }
 }
+// Stores and loads that meet between workgroups of one launch (the XCDs' L2
+// caches are not coherent).
+__device__ __forceinline__ void st_agent(float* p, float v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float ld_agent(const float* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 __device__ __forceinline__ int lanes_below(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
 }
@@ -304,13 +312,13 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
     p = __builtin_amdgcn_readfirstlane(lo);
     c = bx - a.chunk_prefix[p];
   }
-  int S, T, row0, w0, w1;
+  int S, T, row0, seed0, w0, w1;
   if (a.wl.one.S > 0) {
-    S = a.wl.one.S; T = a.wl.one.T; row0 = 0; w0 = a.wl.one.box_lo; w1 = a.wl.one.box_hi;
+    S = a.wl.one.S; T = a.wl.one.T; row0 = 0; seed0 = 0; w0 = a.wl.one.box_lo; w1 = a.wl.one.box_hi;
   } else {
     cv4i* pr = (cv4i*)(a.prob + p);
     const v4i p0 = pr[0], p1 = pr[1];
-    S = p0.x; T = p0.y; row0 = p0.w; w0 = p1.y; w1 = p1.z;
+    S = p0.x; T = p0.y; row0 = p0.w; seed0 = p1.x; w0 = p1.y; w1 = p1.z;
   }
   Problem pb;
   pb.S = S; pb.T = T; pb.world = 0; pb.row0 = row0; pb.seed0 = 0; pb.box_lo = w0; pb.box_hi = w1; pb.pad = 0;
@@ -818,11 +826,52 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
   if (valid && sub == 0) {
     const size_t e = (size_t)k * a.rows + row;
     if (l == 0) {
-      a.cost_e[e] = csum;
-      if (a.mc_e) a.mc_e[e] = mcmin;
-      if (CAND && GRAD) a.gd_e[e] = gd;
+      if (a.sum.count) {
+        // (read by another workgroup below: written through to where every
+        // XCD sees it)
+        st_agent(a.cost_e + e, csum);
+        st_agent(a.mc_e + e, mcmin);
+        if (CAND && GRAD) st_agent(a.gd_e + e, gd);
+      } else {
+        a.cost_e[e] = csum;
+        if (a.mc_e) a.mc_e[e] = mcmin;
+        if (CAND && GRAD) a.gd_e[e] = gd;
+      }
     }
     if (GRAD && l < D) a.grad_e[e * D + l] = gradj;
+  }
+
+  // ---- the seeds' sums: every workgroup adds its rows to its seeds' counts,
+  //      and the one that completes a seed sums the rows, a wave per
+  //      candidate, in the order of reduce_kernel (same bits) ----
+  if (a.sum.count) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's rows are where every XCD sees them
+    __syncthreads();
+    int* s_done = reinterpret_cast<int*>(s_mem);
+    const int sa = first / T, ns = (min(first + RB, nrows) - 1) / T - sa + 1;
+    if (tid < ns) {
+      const int seg = sa + tid, n = min(min(first + RB, nrows), (seg + 1) * T) - max(first, seg * T);
+      int* cnt = a.sum.count + (size_t)(seed0 + seg) * a.K + blockIdx.y;
+      const bool done = __hip_atomic_fetch_add(cnt, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + n == T;
+      if (done) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      s_done[tid] = done;
+    }
+    __syncthreads();
+    for (int i = wave; i < ns * KB; i += kLplWaves) {
+      const int sg = i / KB, kk = blockIdx.y * KB + i % KB;
+      if (!__builtin_amdgcn_readfirstlane(s_done[sg])) continue;
+      const size_t e = (size_t)kk * a.rows + row0 + (sa + sg) * T + min(lane, T - 1);
+      const float cv = ld_agent(a.cost_e + e), mv = ld_agent(a.mc_e + e);
+      const float gv = CAND && GRAD && a.sum.gd ? ld_agent(a.gd_e + e) : 0.0f;
+      const float cs = wave_sum(lane < T ? cv : 0.0f), ms = wave_min(mv);
+      const float gs = CAND && GRAD ? wave_sum(lane < T ? gv : 0.0f) : 0.0f;
+      if (lane == 0) {
+        const size_t o = (size_t)kk * a.sum.n_seeds + seed0 + sa + sg;
+        a.sum.cost[o] = cs;
+        if (a.sum.min_clear) a.sum.min_clear[o] = ms;
+        if (CAND && GRAD && a.sum.gd) a.sum.gd[o] = gs;
+      }
+    }
   }
 }
 

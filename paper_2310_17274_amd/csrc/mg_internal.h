@@ -190,6 +190,17 @@ struct Box {
   float4 q[4];
 };
 
+// Per-seed sums that the evaluation launch makes itself (lane layout): the
+// workgroup that brings a seed's last rows adds them up.
+struct SeedSums {
+  float* cost;             // [K][seeds]
+  float* min_clear;        // [K][seeds] or null
+  float* gd;               // [K][seeds] or null
+  int* count;              // [seeds][K]: rows of the seed that have arrived, zero between
+                           //   launches; null: no sums
+  int n_seeds;
+};
+
 struct EvalArgs {
   Robot rb;
   Lanes ln;
@@ -227,6 +238,7 @@ struct EvalArgs {
   // collision cost times its unit chord / (2 dt), for the speed's gradient on
   // the neighbouring waypoints (speed_adjoint_kernel), or null
   float4* sp_h;            // [K][rows][M]
+  SeedSums sum;            // lane layout: the seeds' sums, made by the same launch
 };
 
 // The speed metric's gradient on the neighbouring waypoints (Eq.(11)): for
