@@ -198,17 +198,17 @@ mg::Robot dev_robot(const mg_ctx* c) {
 }
 
 // The lane layout's spheres: each link's in order along the longest side of
-// their bounding box, cut in the middle into two parts.  Slots [lpe][maxs], the
-// second part from slot maxs / 2 on, then three balls per link: around all its
+// their bounding box, cut in the middle into two parts.  Slots [lpe][2][most
+// spheres of a part], then three balls per link: around all its
 // spheres, the first part, the second (radius -1e30: none).  A part's ball
 // spares the tests of the other half (52 spheres on 7 links, 524288
 // evaluations of one point 223 us without parts, 215 with; with 28 spheres 196
 // and 194; two arms of 120 spheres among 500 cuboids 203 and 184).
 mg_status build_parts(mg_ctx* c) {
-  const int lpe = c->lpe, maxs = c->maxs;
+  const int lpe = c->lpe, half = (c->max_spheres + 1) / 2, slots = 2 * half;
   const float4 none = make_float4(0.0f, 0.0f, 0.0f, -1e30f);
-  std::vector<float4> tab((size_t)lpe * (maxs + 3), none);
-  c->part_spheres = 0;
+  std::vector<float4> tab((size_t)lpe * (slots + 3), none);
+  c->part_spheres = half;
   // a ball around spheres: the centre moves toward the farthest surface by
   // shrinking steps; the radius slightly widened
   auto ball = [&](const float4* q, int n) {
@@ -244,8 +244,8 @@ mg_status build_parts(mg_ctx* c) {
       if (c->sphere_link[m] == l)
         q.push_back(make_float4(c->sphere[4 * m], c->sphere[4 * m + 1], c->sphere[4 * m + 2], c->sphere[4 * m + 3]));
     const int n = (int)q.size(), n0 = (n + 1) / 2;
-    float4* t = &tab[(size_t)l * maxs];
-    float4* bl = &tab[(size_t)lpe * maxs + 3 * l];
+    float4* t = &tab[(size_t)l * slots];
+    float4* bl = &tab[(size_t)lpe * slots + 3 * l];
     if (n0 < n) {
       auto side = [&](auto get) {
         float lo = 3e38f, hi = -3e38f;
@@ -263,8 +263,7 @@ mg_status build_parts(mg_ctx* c) {
     bl[0] = ball(q.data(), n);
     bl[1] = ball(q.data(), n0);
     bl[2] = ball(q.data() + n0, n - n0);
-    for (int i = 0; i < n; ++i) t[i < n0 ? i : maxs / 2 + i - n0] = q[i];
-    c->part_spheres = std::max(c->part_spheres, n0);
+    for (int i = 0; i < n; ++i) t[i < n0 ? i : half + i - n0] = q[i];
   }
   return dev_upload(&c->d_part_sphere, tab);
 }
@@ -385,7 +384,6 @@ mg_status build_lanes(mg_ctx* c) {
 mg::Lanes dev_lanes(const mg_ctx* c) {
   mg::Lanes ln;
   ln.lpe = c->lpe;
-  ln.maxs = c->maxs;
   ln.used = c->part_spheres;
   ln.kb = ln.rb = ln.uni_rows = 0;
   ln.info = c->d_lane_info;
@@ -515,7 +513,9 @@ int pick_slices(const mg_batch* b, long n_evals) {
 int lane_blocks(const mg_batch* b, int hi, int K, mg::EvalArgs& a) {
   const int epb = mg::kBlock / (b->ctx->lpe * kSlices[hi]);
   int kb = 1;
-  while (kb * 2 <= epb && K % (kb * 2) == 0) kb *= 2;
+  // (swept collision: every wave holds neighbouring rows of one candidate)
+  const int kb_max = b->ctx->params.swept ? mg::kBlock / mg::kWave : epb;
+  while (kb * 2 <= kb_max && K % (kb * 2) == 0) kb *= 2;
   int ri = 0;
   while ((1 << ri) < epb / kb) ++ri;
   a.slices = kSlices[hi];

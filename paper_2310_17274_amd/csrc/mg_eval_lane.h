@@ -88,7 +88,9 @@ __device__ __forceinline__ void link_pose(const float4& f0, const float4& f1, co
 // of those that pass the face test, where segments are short) go through a
 // second queue, one (sphere, cuboid) pair and side per lane.  (Traced where
 // the exact term is, 64 lanes waited for the few that step: 6144 rows of two
-// arms among 500 cuboids, K = 4, took 579 us, 440 with the queue.)
+// arms among 500 cuboids, K = 4, took 579 us, 440 with the queue.)  A wave
+// then holds neighbouring rows of one candidate and shares their poses, which
+// lets three workgroups into a CU's LDS instead of two (410 us, now 315).
 // The lanes' sums go back to the owners (evaluation, link) through an LDS
 // row per lane: each owner finds its rows from six ballots of the owners'
 // bits and adds them in lane order, so the results are deterministic.  (LDS
@@ -104,9 +106,9 @@ __device__ __forceinline__ void link_pose(const float4& f0, const float4& f1, co
 // Measured, us per launch (cost and gradient of every candidate), this layout
 // with its best number of copies against the best wave-per-link layout:
 //   524288 single configurations, 40 cuboids (4096 x 32 seeds, K = 4)  216 / 634
-//   64 problems, 84616 rows, 5 to 200 cuboids each, K = 4              150 / 237
-//   two arms, 120 spheres, 500 cuboids, swept, 6144 rows, K = 4        387 / 1075
-//   the same without the sweep                                         183 / 294
+//   64 problems, 84616 rows, 5 to 200 cuboids each, K = 4              151 / 236
+//   two arms, 120 spheres, 500 cuboids, swept, 6144 rows, K = 4        315 / 1074
+//   the same without the sweep                                         180 / 298
 //   128 seeds x 32, 40 cuboids, K = 8                                  16.1 / 24.1
 //   32 seeds x 32, 40 cuboids, K = 8                                   11.1 / 11.6
 //   4 seeds x 32, 10 cuboids, K = 4                                    7.2 / 9.5
@@ -168,7 +170,7 @@ __device__ __forceinline__ int lanes_below(uint64_t m) {
 
 constexpr int kLplWaves = kBlock / kWave;
 constexpr int kLplTile = 64;      // cuboids staged per tile
-constexpr int kLplPairs = 4 * kWave;   // entries of the (group, link, cuboid) queue
+constexpr int kLplPairs = 2 * kWave;   // entries of the (group, link, cuboid) queue
 constexpr int kLplTrace = 5 * kWave / 2;   // entries of the trace queue (two spheres are tested between checks)
 // float4 between the rows of a staged tile (one more than the cuboids: the
 // four rows of a cuboid, read together, then lie in different banks)
@@ -178,17 +180,19 @@ constexpr int kLplStride = kLplTile + 1;
 // Shared: rows of x and of d (or the particle variance), limits and start,
 // goals, tool transforms, sphere slots, the cuboid tile [4][kLplStride]
 // float4, in particle mode the draws; then per wave: link poses (and with
-// swept collision the neighbouring poses and the trace's reach), the
+// swept collision the poses before the wave's rows, after them and of the
+// start, the trace's reach and where each evaluation's neighbours are), the
 // evaluations' and the links' balls, the lanes' sums, and the queues.
-// Most groups of evaluations a wave's links are bounded over.
+// Most groups of evaluations a wave's links are bounded over (one where the
+// balls of several would cost a workgroup per CU).
 __host__ __device__ constexpr int lpl_groups(int lpe, int H) {
   const int epw = kWave / (lpe * H);
-  return epw < 4 ? epw : 4;
+  return lpe > 8 ? 1 : epw < 4 ? epw : 4;
 }
 struct LplLds {
   int x, d, lim, goal, etf, slot, box, eps, wave, wave_size, total;
 };
-__host__ __device__ inline LplLds lpl_lds(int lpe, int H, int rb, int kb, int D, int maxs, bool sw, bool pm) {
+__host__ __device__ inline LplLds lpl_lds(int lpe, int H, int rb, int kb, int D, int slots, bool sw, bool pm) {
   LplLds o;
   const int rs = rb + 8, ow = kWave / H;
   int at = 0;
@@ -202,12 +206,13 @@ __host__ __device__ inline LplLds lpl_lds(int lpe, int H, int rb, int kb, int D,
   o.lim = take(3 * D);
   o.goal = take(kMaxEE * 7);
   o.etf = take(kMaxEE * 12);
-  o.slot = take(lpe * maxs * 4);
+  o.slot = take(lpe * slots * 4);
   o.box = take(kLplStride * 16);
   o.eps = take(pm ? kb * rs * D : 0);
   o.wave = at;
-  o.wave_size = (sw ? 36 : 12) * ow + (sw ? (ow + 3) / 4 * 4 : 0) + 8 * ow + 4 * lpe * lpl_groups(lpe, H) + 8 * (kWave + 2) +
-                (sw ? kLplTrace / 2 : 0) + (kLplPairs + 3 * kWave) / 2;
+  o.wave_size = 12 * ow + (sw ? 36 * lpe + (ow + 3) / 4 * 4 + 8 : 0) + 8 * ow +
+                4 * lpe * (sw ? 1 : lpl_groups(lpe, H)) + 8 * (kWave + 2) + (sw ? kLplTrace / 2 : 0) +
+                (kLplPairs + 3 * kWave) / 2;
   o.total = at + kLplWaves * o.wave_size;
   return o;
 }
@@ -286,7 +291,7 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
   const int lane = tid % kWave;
   const int l = lane % LPE, sub = lane / LPE % H, ew = lane / (LPE * H);
   const int owner = ew * LPE + l;
-  const int D = a.rb.dof, L = a.rb.n_links, maxs = a.ln.maxs, n_ee = a.rb.n_ee;
+  const int D = a.rb.dof, L = a.rb.n_links, slots = 2 * a.ln.used, n_ee = a.rb.n_ee;
   const int KB = a.ln.kb, RB = a.ln.rb;            // candidates and rows per workgroup (KB RB evaluations)
   const int bx = blockIdx.x;
 
@@ -325,16 +330,19 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
   const int nrows = S * T, first = c * RB;         // this workgroup's first row within the problem
 
   // evaluation of this lane: candidates of a row side by side
+  // (swept: a wave's evaluations are neighbouring rows of one candidate, so
+  // that a row's neighbours are evaluations of the wave but at its ends)
   const int ei = wave * EPW + ew;
-  const int k = blockIdx.y * KB + ei % KB;
-  const int rloc = first + ei / KB;
+  const bool by_row = SW && T > 1;
+  const int k = blockIdx.y * KB + (by_row ? ei / RB : ei % KB);
+  const int rloc = first + (by_row ? ei % RB : ei / KB);
   const bool valid = rloc < nrows;
   const int rl = valid ? rloc : nrows - 1;
   const int t = rl % T;                            // waypoint t + 1 of its seed
   const int row = row0 + rl;
   const bool pm = CAND && !GRAD && a.var != nullptr;
 
-  const LplLds o = lpl_lds(LPE, H, RB, KB, D, maxs, SW, pm);
+  const LplLds o = lpl_lds(LPE, H, RB, KB, D, slots, SW, pm);
   float* s_x = s_mem + o.x;
   float* s_d = s_mem + o.d;
   float* s_lim = s_mem + o.lim;
@@ -344,13 +352,17 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
   float4* s_box = reinterpret_cast<float4*>(s_mem + o.box);
   float* s_eps = s_mem + o.eps;
   float* s_w = s_mem + o.wave + wave * o.wave_size;
-  float4* s_T = reinterpret_cast<float4*>(s_w);                            // [3 or 9][OW]
-  float4* s_ball = s_T + (SW ? 9 : 3) * OW;                                // [2][OW], by part
-  float4* s_lball = s_ball + 2 * OW;                                       // [groups][L]
-  float4* s_res = s_lball + LPE * lpl_groups(LPE, H);                                            // [2][kWave + 2]
+  float4* s_T = reinterpret_cast<float4*>(s_w);                            // [3][OW]
+  float4* s_X = s_T + 3 * OW;                                              // [3][3 LPE] (SW)
+  float4* s_ball = s_X + (SW ? 9 * LPE : 0);                               // [2][OW], by part
+  // [groups][L]; swept, only rows of one point have groups, and no neighbours
+  float4* s_lown = s_ball + 2 * OW;
+  float4* s_lball = SW && T == 1 ? s_X : s_lown;
+  float4* s_res = s_lown + LPE * (SW ? 1 : lpl_groups(LPE, H));                                           // [2][kWave + 2]
   unsigned short* s_tq = reinterpret_cast<unsigned short*>(s_res + 2 * (kWave + 2));   // [kLplTrace] (SW)
   float* s_ext = reinterpret_cast<float*>(s_tq + (SW ? kLplTrace : 0));    // [OW] (SW)
-  unsigned short* s_pq = reinterpret_cast<unsigned short*>(s_ext + (SW ? (OW + 3) / 4 * 4 : 0));   // [kLplPairs]
+  int* s_nb = reinterpret_cast<int*>(s_ext + (SW ? (OW + 3) / 4 * 4 : 0));  // [EPW] (SW)
+  unsigned short* s_pq = reinterpret_cast<unsigned short*>(s_nb + (SW ? 8 : 0));         // [kLplPairs]
   unsigned short* s_q = s_pq + kLplPairs;                                  // [3 kWave]
 
   // ---- one round of loads: this lane's link tables, and the staging ----
@@ -359,7 +371,7 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
   const float4 F0 = reinterpret_cast<const float4*>(a.rb.fixed_tf + lj * 12)[0];
   const float4 F1 = reinterpret_cast<const float4*>(a.rb.fixed_tf + lj * 12)[1];
   const float4 F2 = reinterpret_cast<const float4*>(a.rb.fixed_tf + lj * 12)[2];
-  const float4* bls = a.ln.sphere + LPE * maxs + 3 * l;
+  const float4* bls = a.ln.sphere + LPE * slots + 3 * l;
   const float4 bl = bls[0], bl0 = bls[1], bl1 = bls[2];
   const int r_lo = max(row0, row0 + first - 4);
   const int r_hi = min(row0 + nrows - 1, row0 + first + RB - 1 + 4);
@@ -374,7 +386,7 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
   if (tid < 3 * D) s_lim[tid] = tid < D ? a.rb.q_lo[tid] : tid < 2 * D ? a.rb.q_hi[tid - D] : a.q_start[(size_t)p * D + tid - 2 * D];
   else if (tid >= kWave && tid < kWave + n_ee * 7) s_goal[tid - kWave] = a.goal[(size_t)p * n_ee * 7 + tid - kWave];
   else if (tid >= 2 * kWave && tid < 2 * kWave + n_ee * 12) s_etf[tid - 2 * kWave] = a.rb.ee_tf[tid - 2 * kWave];
-  for (int i = tid; i < LPE * maxs; i += kBlock) s_slot[i] = a.ln.sphere[i];
+  for (int i = tid; i < LPE * slots; i += kBlock) s_slot[i] = a.ln.sphere[i];
   auto stage_tile = [&](int tl) {
     const int nb = min(kLplTile, w1 - tl);
     const float4* src = reinterpret_cast<const float4*>(a.box + tl);
@@ -431,52 +443,58 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
   const float ql = qval(row, lj);
   float Tm[12];
   link_pose<LPE>(F0, F1, F2, on, pos, ql, Tm);
-  float ext = 0.0f;
-  const bool sweep = SW && T > 1;
-  if constexpr (SW) {
-    // link poses at the neighbouring waypoints (the start before waypoint 1;
-    // none after the last: its own pose, a segment of length zero)
-    float Tp[12], Tn[12];
-    if (sweep) {
-      const bool nxt = t + 1 < T;
-      const float qp = t >= 1 ? qval(row - 1, lj) : s_lim[2 * D + lj];
-      const float qn = nxt ? qval(row + 1, lj) : ql;
-      link_pose<LPE>(F0, F1, F2, on, pos, qp, Tp);
-      link_pose<LPE>(F0, F1, F2, on, pos, qn, Tn);
-#pragma unroll
-      for (int e = 0; e < 12; ++e) Tn[e] = nxt ? Tn[e] : Tm[e];
-      // the cull's reach: half the longest segment over the link's spheres
-      // (slightly widened so rounding never culls a sample the trace takes)
-      float l2 = 0.0f;
-      for (int s = 0; s < maxs; ++s) {
-        const float4 ls = s_slot[l * maxs + s];
-        if (ls.w <= -1e29f) continue;
-        auto seg2 = [&](const float* N) {
-          const float ux = (N[0] - Tm[0]) * ls.x + (N[1] - Tm[1]) * ls.y + (N[2] - Tm[2]) * ls.z + (N[3] - Tm[3]);
-          const float uy = (N[4] - Tm[4]) * ls.x + (N[5] - Tm[5]) * ls.y + (N[6] - Tm[6]) * ls.z + (N[7] - Tm[7]);
-          const float uz = (N[8] - Tm[8]) * ls.x + (N[9] - Tm[9]) * ls.y + (N[10] - Tm[10]) * ls.z + (N[11] - Tm[11]);
-          return ux * ux + uy * uy + uz * uz;
-        };
-        l2 = fmaxf(l2, fmaxf(seg2(Tp), seg2(Tn)));
-      }
-      ext = 0.5f * sqrtf(l2) * 1.001f + 1e-6f;
-    } else {
-#pragma unroll
-      for (int e = 0; e < 12; ++e) Tp[e] = Tn[e] = Tm[e];
-    }
-    if (sub == 0) {
-#pragma unroll
-      for (int r = 0; r < 3; ++r) {
-        s_T[(3 + r) * OW + owner] = make_float4(Tp[4 * r], Tp[4 * r + 1], Tp[4 * r + 2], Tp[4 * r + 3]);
-        s_T[(6 + r) * OW + owner] = make_float4(Tn[4 * r], Tn[4 * r + 1], Tn[4 * r + 2], Tn[4 * r + 3]);
-      }
-      s_ext[owner] = ext;
-    }
-  }
   if (sub == 0) {
 #pragma unroll
     for (int r = 0; r < 3; ++r)
       s_T[r * OW + owner] = make_float4(Tm[4 * r], Tm[4 * r + 1], Tm[4 * r + 2], Tm[4 * r + 3]);
+  }
+  float ext = 0.0f;
+  if constexpr (SW) {
+    if (T > 1) {
+      // link poses at the neighbouring waypoints (the start before waypoint 1;
+      // none after the last: its own pose, a segment of length zero): other
+      // evaluations', or the three that lanes 0, LPE and 2 LPE on form here
+      const int w_lo = first + wave * EPW % RB, g = lane / LPE;
+      const int r_a = max(min(w_lo, nrows - 1) - 1, 0), r_b = min(w_lo + EPW, nrows - 1);
+      const float qx = g == 2 ? s_lim[2 * D + lj] : qval(row0 + (g == 0 ? max(r_a, r_lo - row0) : r_b), lj);
+      float Tx[12];
+      link_pose<LPE>(F0, F1, F2, on, pos, qx, Tx);
+      if (g < 3) {
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+          s_X[(3 * r + g) * LPE + l] = make_float4(Tx[4 * r], Tx[4 * r + 1], Tx[4 * r + 2], Tx[4 * r + 3]);
+      }
+      const int prev = t == 0 ? EPW + 2 : ew == 0 ? EPW : ew - 1;
+      const int next = t + 1 == T ? ew : ew == EPW - 1 ? EPW + 1 : ew + 1;
+      if (l == 0 && sub == 0) s_nb[ew] = prev | next << 8;
+      wave_lds_fence();
+      // the cull's reach: half the longest segment over the link's spheres
+      // (slightly widened so rounding never culls a sample the trace takes)
+      float4 dp[3], dn[3];
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        auto diff = [&](int sl) {
+          const float4 v = sl < EPW ? s_T[r * OW + sl * LPE + l] : s_X[(3 * r + sl - EPW) * LPE + l];
+          return make_float4(v.x - Tm[4 * r], v.y - Tm[4 * r + 1], v.z - Tm[4 * r + 2], v.w - Tm[4 * r + 3]);
+        };
+        dp[r] = diff(prev);
+        dn[r] = diff(next);
+      }
+      float l2 = 0.0f;
+      for (int s = 0; s < slots; ++s) {
+        const float4 ls = s_slot[l * slots + s];
+        if (ls.w <= -1e29f) continue;
+        auto seg2 = [&](const float4* N) {
+          const float ux = N[0].x * ls.x + N[0].y * ls.y + N[0].z * ls.z + N[0].w;
+          const float uy = N[1].x * ls.x + N[1].y * ls.y + N[1].z * ls.z + N[1].w;
+          const float uz = N[2].x * ls.x + N[2].y * ls.y + N[2].z * ls.z + N[2].w;
+          return ux * ux + uy * uy + uz * uz;
+        };
+        l2 = fmaxf(l2, fmaxf(seg2(dp), seg2(dn)));
+      }
+      ext = 0.5f * sqrtf(l2) * 1.001f + 1e-6f;
+    }
+    if (sub == 0) s_ext[owner] = ext;
   }
   // the ball around the link's spheres, widened slightly so rounding never
   // drops a cuboid that matters (a lane without spheres never passes)
@@ -517,7 +535,7 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
   wave_lds_fence();
 
   // ---- the near pairs ----
-  const int used = a.ln.used;                      // most spheres on any link
+  const int used = a.ln.used;                      // most spheres of a part
   // this lane's sums as an owner (copy sub of an evaluation adds the rows of
   // its share of the lanes): cost, clearance, force and moment about the
   // world origin
@@ -586,8 +604,11 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
       const float4 A0 = s_box[ob], A1 = s_box[kLplStride + ob], A2 = s_box[2 * kLplStride + ob],
                    Hh = s_box[3 * kLplStride + ob];
       const float4 t0 = s_T[ow], t1 = s_T[OW + ow], t2 = s_T[2 * OW + ow];
-      const float4 n0 = s_T[3 * side * OW + ow], n1 = s_T[(3 * side + 1) * OW + ow], n2 = s_T[(3 * side + 2) * OW + ow];
-      const float4 ls = s_slot[(ow % LPE) * maxs + sl];
+      const int nb = s_nb[ow / LPE], nsl = side == 1 ? nb & 255 : nb >> 8;
+      const float4* nt = nsl < EPW ? s_T + nsl * LPE + ow % LPE : s_X + (nsl - EPW) * LPE + ow % LPE;
+      const int nst = nsl < EPW ? OW : 3 * LPE;
+      const float4 n0 = nt[0], n1 = nt[nst], n2 = nt[2 * nst];
+      const float4 ls = s_slot[(ow % LPE) * slots + sl];
       const float cx = t0.x * ls.x + t0.y * ls.y + t0.z * ls.z + t0.w;
       const float cy = t1.x * ls.x + t1.y * ls.y + t1.z * ls.z + t1.w;
       const float cz = t2.x * ls.x + t2.y * ls.y + t2.z * ls.z + t2.w;
@@ -621,11 +642,11 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
     const int ii = lane & (per - 1);
     const bool act = ii < n;
     const unsigned it = act ? q[ii] : 0;
-    const int ow = it & 63, s_h = (it >> 6 & 1) * (maxs / 2), ob = it >> 7;
+    const int ow = it & 63, s_h = (it >> 6 & 1) * used, ob = it >> 7;
     const float4 A0 = s_box[ob], A1 = s_box[kLplStride + ob], A2 = s_box[2 * kLplStride + ob],
                  Hh = s_box[3 * kLplStride + ob];
     const float4 t0 = s_T[ow], t1 = s_T[OW + ow], t2 = s_T[2 * OW + ow];
-    const float4* sl = s_slot + (ow % LPE) * maxs + s_h;
+    const float4* sl = s_slot + (ow % LPE) * slots + s_h;
     const float ext_o = SW ? s_ext[ow] : 0.0f;
     const float reach = act ? eta + ext_o : -1e30f;
     const int s1 = lane >> (6 - sh);               // this lane's spheres: s1, s1 + (1 << sh), ..
@@ -882,10 +903,11 @@ hipError_t launch_eval_sw(const EvalArgs& a, int grid_x, bool cand, bool grad, h
   // the workgroup's evaluations are KB candidates (a divisor of K) of RB rows
   const int K = cand ? a.K : 1;
   if (a.ln.kb < 1 || a.ln.kb * a.ln.rb != epb || K % a.ln.kb || (pm && (!cand || grad)) || a.ln.lpe != LPE ||
-      a.ln.maxs > 16 || a.ln.used > a.ln.maxs || a.rb.dof > a.rb.n_links || a.rb.n_links > LPE || grid_x < 1)
+      a.ln.used > 8 || (SW && a.ln.rb % (epb / kLplWaves)) || a.rb.dof > a.rb.n_links || a.rb.n_links > LPE ||
+      grid_x < 1)
     return hipErrorInvalidValue;
   const dim3 grid(grid_x, K / a.ln.kb), block(kBlock);
-  const size_t lds = (size_t)lpl_lds(LPE, H, a.ln.rb, a.ln.kb, a.rb.dof, a.ln.maxs, SW, pm).total * sizeof(float);
+  const size_t lds = (size_t)lpl_lds(LPE, H, a.ln.rb, a.ln.kb, a.rb.dof, 2 * a.ln.used, SW, pm).total * sizeof(float);
   auto go = [&](auto kern) -> hipError_t {
     if (lds > 64 * 1024) {
       const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),

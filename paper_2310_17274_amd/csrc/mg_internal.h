@@ -68,14 +68,13 @@ struct Robot {
 // its spheres and (if l < D) joint l.
 struct Lanes {
   int lpe;                 // lanes per evaluation: 8 or 16
-  int maxs;                // sphere slots per link: 4, 8 or 16
   int used;                // most spheres of a part
   int kb, rb;              // a workgroup's evaluations: kb candidates (dividing K) of rb rows
   int uni_rows;            // > 0: every problem has this many rows (S T)
   const int4* info;        // [lpe]: chain start lane, chain end lane, spheres, end effector or -1
-  const float4* sphere;    // [lpe][maxs] center in link frame + radius (-1e30: no sphere), the
-                           //   second part of a link from slot maxs / 2 on; then [lpe][3] balls
-                           //   around all spheres of the link, its first part, its second
+  const float4* sphere;    // [lpe][2][used] center in link frame + radius (-1e30: no sphere), the
+                           //   spheres of a link's two parts; then [lpe][3] balls around all
+                           //   spheres of the link, its first part, its second
 };
 
 // One 64-evaluation chunk of the wave-per-link layout: its problem, its
