@@ -192,7 +192,8 @@ __host__ __device__ constexpr int lpl_groups(int lpe, int H) {
 struct LplLds {
   int x, d, lim, goal, etf, slot, box, eps, wave, wave_size, total;
 };
-__host__ __device__ inline LplLds lpl_lds(int lpe, int H, int rb, int kb, int D, int slots, bool sw, bool pm) {
+__host__ __device__ inline LplLds lpl_lds(int lpe, int H, int rb, int kb, int D, int slots, bool sw, bool pm,
+                                         bool grad) {
   LplLds o;
   const int rs = rb + 8, ow = kWave / H;
   int at = 0;
@@ -211,7 +212,7 @@ __host__ __device__ inline LplLds lpl_lds(int lpe, int H, int rb, int kb, int D,
   o.eps = take(pm ? kb * rs * D : 0);
   o.wave = at;
   o.wave_size = 12 * ow + (sw ? 36 * lpe + (ow + 3) / 4 * 4 + 8 : 0) + 8 * ow +
-                4 * lpe * (sw ? 1 : lpl_groups(lpe, H)) + 8 * (kWave + 2) + (sw ? kLplTrace / 2 : 0) +
+                4 * lpe * (sw ? 1 : lpl_groups(lpe, H)) + (grad ? 8 : 4) * (kWave + 2) + (sw ? kLplTrace / 2 : 0) +
                 (kLplPairs + 3 * kWave) / 2;
   o.total = at + kLplWaves * o.wave_size;
   return o;
@@ -342,7 +343,7 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
   const int row = row0 + rl;
   const bool pm = CAND && !GRAD && a.var != nullptr;
 
-  const LplLds o = lpl_lds(LPE, H, RB, KB, D, slots, SW, pm);
+  const LplLds o = lpl_lds(LPE, H, RB, KB, D, slots, SW, pm, GRAD);
   float* s_x = s_mem + o.x;
   float* s_d = s_mem + o.d;
   float* s_lim = s_mem + o.lim;
@@ -358,8 +359,8 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
   // [groups][L]; swept, only rows of one point have groups, and no neighbours
   float4* s_lown = s_ball + 2 * OW;
   float4* s_lball = SW && T == 1 ? s_X : s_lown;
-  float4* s_res = s_lown + LPE * (SW ? 1 : lpl_groups(LPE, H));                                           // [2][kWave + 2]
-  unsigned short* s_tq = reinterpret_cast<unsigned short*>(s_res + 2 * (kWave + 2));   // [kLplTrace] (SW)
+  float4* s_res = s_lown + LPE * (SW ? 1 : lpl_groups(LPE, H));                                           // [2 with GRAD][kWave + 2]
+  unsigned short* s_tq = reinterpret_cast<unsigned short*>(s_res + (GRAD ? 2 : 1) * (kWave + 2));   // [kLplTrace] (SW)
   float* s_ext = reinterpret_cast<float*>(s_tq + (SW ? kLplTrace : 0));    // [OW] (SW)
   int* s_nb = reinterpret_cast<int*>(s_ext + (SW ? (OW + 3) / 4 * 4 : 0));  // [EPW] (SW)
   unsigned short* s_pq = reinterpret_cast<unsigned short*>(s_nb + (SW ? 8 : 0));         // [kLplPairs]
@@ -590,7 +591,7 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
   };
   if (lane < 2) {
     s_res[kWave + lane] = make_float4(0.0f, 3.0e38f, 0.0f, 0.0f);
-    s_res[2 * kWave + 2 + lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (GRAD) s_res[2 * kWave + 2 + lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   }
   int ntq = 0;                                     // traces pending (SW)
   // up to 32 (owner, sphere, cuboid), one per lane and side: the trace toward
@@ -907,7 +908,7 @@ hipError_t launch_eval_sw(const EvalArgs& a, int grid_x, bool cand, bool grad, h
       grid_x < 1)
     return hipErrorInvalidValue;
   const dim3 grid(grid_x, K / a.ln.kb), block(kBlock);
-  const size_t lds = (size_t)lpl_lds(LPE, H, a.ln.rb, a.ln.kb, a.rb.dof, 2 * a.ln.used, SW, pm).total * sizeof(float);
+  const size_t lds = (size_t)lpl_lds(LPE, H, a.ln.rb, a.ln.kb, a.rb.dof, 2 * a.ln.used, SW, pm, grad).total * sizeof(float);
   auto go = [&](auto kern) -> hipError_t {
     if (lds > 64 * 1024) {
       const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
