@@ -874,8 +874,11 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
     if (tid < ns) {
       const int seg = sa + tid, n = min(min(first + RB, nrows), (seg + 1) * T) - max(first, seg * T);
       int* cnt = a.sum.count + (size_t)(seed0 + seg) * a.K + blockIdx.y;
-      const bool done = __hip_atomic_fetch_add(cnt, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + n == T;
-      if (done) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      // (whole seeds are taken off again, not the count cleared: it returns to
+      // zero whatever launches of one batch overlap)
+      const int old = __hip_atomic_fetch_add(cnt, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const bool done = (unsigned)old / T != (unsigned)(old + n) / T;
+      if (done) __hip_atomic_fetch_add(cnt, -T, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       s_done[tid] = done;
     }
     __syncthreads();
