@@ -1363,10 +1363,10 @@ mg_status mg_autotune(mg_ctx* c, mg_batch* b, const float* q_start, const float*
       b->wl_groups = 1;
       return st;
     }
-    // a layout in which the solve folds its choice in saves about 2 us per
+    // a layout in which the solve folds its choice in saves 1 to 2.5 us per
     // iteration: a launch of the choice costs 5.1 to 5.5 with its gap, folded
     // in it delays the evaluation by 2.6 (few near pairs) to 4.1 (many)
-    if (opts[o].layout == 1 && fuse_ok(c, b, K, std::min(4, b->m_max), nullptr)) us -= 2.0f;
+    if (opts[o].layout == 1 && fuse_ok(c, b, K, std::min(4, b->m_max), nullptr)) us -= 1.5f;
     if (us < best_us) { best_us = us; best = o; }
   }
   b->layout = opts[best].layout;

@@ -176,6 +176,13 @@ constexpr int kLplTrace = 5 * kWave / 2;   // entries of the trace queue (two sp
 // four rows of a cuboid, read together, then lie in different banks)
 constexpr int kLplStride = kLplTile + 1;
 
+// Most groups of evaluations a wave's links are bounded over (one where the
+// balls of several would cost a workgroup per CU).
+__host__ __device__ constexpr int lpl_groups(int lpe, int H) {
+  const int epw = kWave / (lpe * H);
+  return lpe > 8 ? 1 : epw < 4 ? epw : 4;
+}
+
 // LDS of a lane-per-link workgroup, float offsets (kept a multiple of 4).
 // Shared: rows of x and of d (or the particle variance), limits and start,
 // goals, tool transforms, sphere slots, the cuboid tile [4][kLplStride]
@@ -183,12 +190,6 @@ constexpr int kLplStride = kLplTile + 1;
 // swept collision the poses before the wave's rows, after them and of the
 // start, the trace's reach and where each evaluation's neighbours are), the
 // evaluations' and the links' balls, the lanes' sums, and the queues.
-// Most groups of evaluations a wave's links are bounded over (one where the
-// balls of several would cost a workgroup per CU).
-__host__ __device__ constexpr int lpl_groups(int lpe, int H) {
-  const int epw = kWave / (lpe * H);
-  return lpe > 8 ? 1 : epw < 4 ? epw : 4;
-}
 struct LplLds {
   int x, d, lim, goal, etf, slot, box, eps, wave, wave_size, total;
 };
