@@ -488,8 +488,12 @@ mg_status check_params(const mg_params* p) {
 
 // Lane-per-link copies (an index into kSlices) for a call evaluating n_evals
 // rows x candidates: the fewest (least repeated kinematics) that still give
-// every SIMD about kLplTarget wavefronts; MG_CUBOID_SLICES forces a choice.
-// A choice of the autotuner holds for the number of evaluations it timed.
+// every SIMD a wavefront, and more than one unless every SIMD has two without
+// (us per launch with one copy and two, 7 joints: 8192 evaluations 11.5 / 10.9
+// in a sparse world, 17.6 / 14.5 in a dense one; 12288 12.8 / 12.6 and 18.0 /
+// 16.6; 16384 12.2 / 14.6 and 19.3 / 19.4; two arms, swept: 6144 149 / 111,
+// 12288 176 / 202).  MG_CUBOID_SLICES forces a choice; one of the autotuner
+// holds for the number of evaluations it timed.
 int pick_slices(const mg_batch* b, long n_evals) {
   const int n_opts = b->ctx->lpe == 8 ? kNumSlices : kNumSlices - 1;
   if (b->slices >= 0 && (b->layout_set || n_evals == b->tuned_evals)) return b->slices;
@@ -500,9 +504,9 @@ int pick_slices(const mg_batch* b, long n_evals) {
       if (kSlices[i] == h) return i;
   }
   const long waves1 = (n_evals * b->ctx->lpe + mg::kWave - 1) / mg::kWave;
-  const long target = 256L * 4;   // CUs x SIMDs
+  const long simds = 256L * 4;
   for (int i = 0; i < n_opts; ++i)
-    if (waves1 * kSlices[i] >= target) return i;
+    if (waves1 * kSlices[i] >= (i == 0 ? 2 * simds : simds)) return i;
   return n_opts - 1;
 }
 
