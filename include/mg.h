@@ -264,6 +264,11 @@ mg_status mg_ee_pose(mg_ctx *ctx, int rows, const float *q, float *pose, void *s
  * 16 evaluations per workgroup, each quarter of a wave testing a quarter of
  * the slots (four times the workgroups; at least 8 slots per link).  In
  * both, two lane groups split each evaluation's kinematic chain in halves.
+ * The layouts' results agree to rounding but where a decision hangs on the
+ * last bit of a pose (two faces of a cuboid equally near a sphere's centre
+ * deep inside it, a trace that meets a surface head on): there a gradient may
+ * follow the other face.  An autotuned batch of a robot of more than 8 links
+ * decides as layout 1 does, whichever layout runs.
  * mg_batch_set_layout fixes a layout (-1: library default, 0 .. 4) and a
  * slice count (0: automatic; 1, 2 or 4, and for layout 1 also 8 or 16;
  * layouts 2, 3 and 4 take 0 or 1).

@@ -385,7 +385,7 @@ mg::Lanes dev_lanes(const mg_ctx* c) {
   mg::Lanes ln;
   ln.lpe = c->lpe;
   ln.used = c->part_spheres;
-  ln.kb = ln.rb = ln.uni_rows = 0;
+  ln.kb = ln.rb = ln.uni_rows = ln.serial = 0;
   ln.info = c->d_lane_info;
   ln.sphere = c->d_part_sphere;
   return ln;
@@ -530,6 +530,23 @@ int lane_blocks(const mg_batch* b, int hi, int K, mg::EvalArgs& a) {
   return b->chunks[ri];
 }
 
+// Whether a lane-per-link launch forms poses as the wave-per-link layout
+// does.  The layouts agree to rounding, but where a sphere's centre lies deep in
+// a cuboid with two faces equally near, or a trace's sample at the end of its
+// half segment, the last bit of a pose decides on which normal the gradient
+// points along or on whether the sample counts.  A caller who has the layout
+// chosen (by the autotuner, or by the particle stage where it traces) gets
+// those decisions as wave per link makes them, whichever layout is the
+// fastest.  Robots of up to 8 links without traces keep the prefix product when
+// tuned: their wave-per-link layout splits the chain in halves, with bits of
+// its own.  (Two arms, 120 spheres, 500 cuboids, swept, 6144 rows, K = 4: 259 us
+// a call link by link, 254 by prefix product.)
+bool serial_poses(const mg_batch* b, bool particles) {
+  const mg_ctx* c = b->ctx;
+  if (b->layout_set) return false;
+  return particles ? c->params.swept != 0 : b->tuned_evals > 0 && (c->L > 8 || c->params.swept);
+}
+
 // One problem: the wave-per-link kernel forms its chunk records from the
 // workgroup index (the same records the table holds).
 void wl_single(const mg_batch* b, int K, mg::WaveLinks& wl) {
@@ -557,6 +574,7 @@ mg::EvalArgs eval_args(const mg_ctx* c, const mg_batch* b, int hi, const float* 
   a.prob = b->d_prob;
   lane_blocks(b, hi, K, a);
   wl_single(b, K, a.wl);
+  a.ln.serial = serial_poses(b, false);
   a.P = b->P;
   a.rows = b->rows;
   a.box = c->d_box;
@@ -1552,6 +1570,7 @@ mg_status particle_rounds(mg_ctx* c, mg_batch* b, const float* q_start, const fl
     }
     mg::EvalArgs a = eval_args(c, b, hi, q_start, goal, mean, e, n_particles, nullptr);
     a.var = var;
+    a.ln.serial = serial_poses(b, true);
     if (e) a.d_stride = (size_t)b->rows * c->D;
     else a.pm_seed = seed;
     a.pm_it = it;

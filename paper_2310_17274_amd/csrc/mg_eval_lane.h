@@ -64,6 +64,35 @@ __device__ __forceinline__ void link_pose(const float4& f0, const float4& f1, co
   if (LPE > 8) scan_step<8>(T, pos >= 8);
 }
 
+// The same pose formed link by link from the root, with the operations of the
+// wave-per-link layout's chain_fk (`steps` links follow the first on the longest
+// chain): bit for bit its pose.
+__device__ __forceinline__ void link_pose_serial(const float4& f0, const float4& f1, const float4& f2, bool on,
+                                                 int pos, int steps, float q, float* T) {
+  const float sn = __sinf(q), cs = __cosf(q);
+  T[0] = f0.x * cs + f0.y * sn;  T[1] = f0.y * cs - f0.x * sn;  T[2] = f0.z;  T[3] = f0.w;
+  T[4] = f1.x * cs + f1.y * sn;  T[5] = f1.y * cs - f1.x * sn;  T[6] = f1.z;  T[7] = f1.w;
+  T[8] = f2.x * cs + f2.y * sn;  T[9] = f2.y * cs - f2.x * sn;  T[10] = f2.z; T[11] = f2.w;
+  // (step i leaves the poses of the chains' first i + 1 links as they are)
+  for (int i = 0; i < steps; ++i) {
+    float P[12];
+    dpp12<0x111>(T, P);                // row_shr:1, the parent's pose
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      const float t0 = P[r * 4 + 0], t1 = P[r * 4 + 1], t2 = P[r * 4 + 2], t3 = P[r * 4 + 3];
+      const float u0 = t0 * f0.x + t1 * f1.x + t2 * f2.x;
+      const float u1 = t0 * f0.y + t1 * f1.y + t2 * f2.y;
+      const float u2 = t0 * f0.z + t1 * f1.z + t2 * f2.z;
+      const float u3 = t0 * f0.w + t1 * f1.w + t2 * f2.w + t3;
+      T[r * 4 + 0] = pos >= 1 ? u0 * cs + u1 * sn : T[r * 4 + 0];
+      T[r * 4 + 1] = pos >= 1 ? u1 * cs - u0 * sn : T[r * 4 + 1];
+      T[r * 4 + 2] = pos >= 1 ? u2 : T[r * 4 + 2];
+      T[r * 4 + 3] = pos >= 1 ? u3 : T[r * 4 + 3];
+    }
+  }
+  if (!on) identity(T);
+}
+
 // Lane l of an evaluation owns link l (its pose, sphere ball, joint and
 // pose terms); an evaluation takes LPE lanes (8 or 16, one per link) times H
 // copies that split the world's cuboids, and a wave holds 64 / (LPE H)
@@ -253,21 +282,37 @@ __device__ __forceinline__ void pair_term(float px, float py, float pz, float ax
   }
 }
 
-// The trace toward one neighbouring waypoint (Alg.11-12) in the box frame:
-// direction u (unscaled), from p with distance sdf.
+// A link-frame point in the world: row r of the pose (a, w) times (x, y, z, 1).
+// (Spelled out, as the compiler contracts the same sum in the wave-per-link
+// kernels: left to itself it picks the order of the products by their operands.)
+__device__ __forceinline__ float dot3(float ax, float ay, float az, float x, float y, float z) {
+  return fmaf(az, z, fmaf(ax, x, ay * y));
+}
+__device__ __forceinline__ float row_point(const float4& a, const float4& p) {
+  return dot3(a.x, a.y, a.z, p.x, p.y, p.z) + a.w;
+}
+
+// The trace toward one neighbouring waypoint (Alg.11-12): direction u (world,
+// unscaled), from p (box frame) with distance sdf; the samples' gradients in
+// the box frame.  (The operations of the wave-per-link layout's
+// sweep_pair_box: where a sample lies decides whether it counts at all.)
 template <bool GRAD>
-__device__ __forceinline__ void trace_term(float ux, float uy, float uz, int steps, float px, float py, float pz,
+__device__ __forceinline__ void trace_term(float ux, float uy, float uz, const float4& A0, const float4& A1,
+                                           const float4& A2, int steps, float px, float py, float pz,
                                            const float4& Hh, float sdf, float r, float w, float eta, float inv_eta,
                                            float& cost, float* b) {
   const float rh = r + eta;
-  const float len = sqrtf(ux * ux + uy * uy + uz * uz);
+  const float len = sqrtf(dot3(ux, uy, uz, ux, uy, uz));
   const float half = 0.5f * len;
   float j = sdf < rh ? rh : sdf - rh;
   if (!(len > 0.0f && j < half)) return;
   const float il = 1.0f / len;
   ux *= il; uy *= il; uz *= il;
+  const float vx = dot3(A0.x, A0.y, A0.z, ux, uy, uz);
+  const float vy = dot3(A1.x, A1.y, A1.z, ux, uy, uz);
+  const float vz = dot3(A2.x, A2.y, A2.z, ux, uy, uz);
   for (int st = 0; st < steps && j < half; ++st) {
-    const float qx = fmaf(j, ux, px), qy = fmaf(j, uy, py), qz = fmaf(j, uz, pz);
+    const float qx = fmaf(j, vx, px), qy = fmaf(j, vy, py), qz = fmaf(j, vz, pz);
     float s2;
     if (GRAD) {
       float gx, gy, gz;
@@ -443,8 +488,12 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
   const bool on = l < L;
   const int pos = l - info.x;
   const float ql = qval(row, lj);
+  auto pose_at = [&](float q, float* To) {
+    if (a.ln.serial) link_pose_serial(F0, F1, F2, on, pos, a.wl.max_depth - 1, q, To);
+    else link_pose<LPE>(F0, F1, F2, on, pos, q, To);
+  };
   float Tm[12];
-  link_pose<LPE>(F0, F1, F2, on, pos, ql, Tm);
+  pose_at(ql, Tm);
   if (sub == 0) {
 #pragma unroll
     for (int r = 0; r < 3; ++r)
@@ -460,7 +509,7 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
       const int r_a = max(min(w_lo, nrows - 1) - 1, 0), r_b = min(w_lo + EPW, nrows - 1);
       const float qx = g == 2 ? s_lim[2 * D + lj] : qval(row0 + (g == 0 ? max(r_a, r_lo - row0) : r_b), lj);
       float Tx[12];
-      link_pose<LPE>(F0, F1, F2, on, pos, qx, Tx);
+      pose_at(qx, Tx);
       if (g < 3) {
 #pragma unroll
         for (int r = 0; r < 3; ++r)
@@ -611,20 +660,19 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
       const int nst = nsl < EPW ? OW : 3 * LPE;
       const float4 n0 = nt[0], n1 = nt[nst], n2 = nt[2 * nst];
       const float4 ls = s_slot[(ow % LPE) * slots + sl];
-      const float cx = t0.x * ls.x + t0.y * ls.y + t0.z * ls.z + t0.w;
-      const float cy = t1.x * ls.x + t1.y * ls.y + t1.z * ls.z + t1.w;
-      const float cz = t2.x * ls.x + t2.y * ls.y + t2.z * ls.z + t2.w;
+      const float cx = row_point(t0, ls);
+      const float cy = row_point(t1, ls);
+      const float cz = row_point(t2, ls);
       const float px = fmaf(A0.x, cx, fmaf(A0.y, cy, fmaf(A0.z, cz, A0.w)));
       const float py = fmaf(A1.x, cx, fmaf(A1.y, cy, fmaf(A1.z, cz, A1.w)));
       const float pz = fmaf(A2.x, cx, fmaf(A2.y, cy, fmaf(A2.z, cz, A2.w)));
-      // the segment from the poses' difference, box frame
-      const float ux = (n0.x - t0.x) * ls.x + (n0.y - t0.y) * ls.y + (n0.z - t0.z) * ls.z + (n0.w - t0.w);
-      const float uy = (n1.x - t1.x) * ls.x + (n1.y - t1.y) * ls.y + (n1.z - t1.z) * ls.z + (n1.w - t1.w);
-      const float uz = (n2.x - t2.x) * ls.x + (n2.y - t2.y) * ls.y + (n2.z - t2.z) * ls.z + (n2.w - t2.w);
+      // the segment to the neighbouring waypoint's centre
+      const float ux = row_point(n0, ls) - cx;
+      const float uy = row_point(n1, ls) - cy;
+      const float uz = row_point(n2, ls) - cz;
       float cost = 0.0f, b[3] = {0.0f, 0.0f, 0.0f};
       if (act)
-        trace_term<GRAD>(A0.x * ux + A0.y * uy + A0.z * uz, A1.x * ux + A1.y * uy + A1.z * uz,
-                         A2.x * ux + A2.y * uy + A2.z * uz, a.pr.sweep_steps, px, py, pz, Hh,
+        trace_term<GRAD>(ux, uy, uz, A0, A1, A2, a.pr.sweep_steps, px, py, pz, Hh,
                          box_dist(fabsf(px) - Hh.x, fabsf(py) - Hh.y, fabsf(pz) - Hh.z), ls.w, wc, eta, inv_eta, cost,
                          b);
       const bool some = cost != 0.0f;
@@ -656,9 +704,9 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
     // (the face test; an unused slot's radius is -1e30: it never passes)
     auto test = [&](int s, float4& ls, float* p, float& m3) -> bool {
       ls = sl[min(s, used - 1)];
-      const float cx = t0.x * ls.x + t0.y * ls.y + t0.z * ls.z + t0.w;
-      const float cy = t1.x * ls.x + t1.y * ls.y + t1.z * ls.z + t1.w;
-      const float cz = t2.x * ls.x + t2.y * ls.y + t2.z * ls.z + t2.w;
+      const float cx = row_point(t0, ls);
+      const float cy = row_point(t1, ls);
+      const float cz = row_point(t2, ls);
       p[0] = fmaf(A0.x, cx, fmaf(A0.y, cy, fmaf(A0.z, cz, A0.w)));
       p[1] = fmaf(A1.x, cx, fmaf(A1.y, cy, fmaf(A1.z, cz, A1.w)));
       p[2] = fmaf(A2.x, cx, fmaf(A2.y, cy, fmaf(A2.z, cz, A2.w)));

@@ -71,6 +71,8 @@ struct Lanes {
   int used;                // most spheres of a part
   int kb, rb;              // a workgroup's evaluations: kb candidates (dividing K) of rb rows
   int uni_rows;            // > 0: every problem has this many rows (S T)
+  int serial;              // poses link by link from the root (the wave-per-link layout's bits), not
+                           //   by a prefix product
   const int4* info;        // [lpe]: chain start lane, chain end lane, spheres, end effector or -1
   const float4* sphere;    // [lpe][2][used] center in link frame + radius (-1e30: no sphere), the
                            //   spheres of a link's two parts; then [lpe][3] balls around all
