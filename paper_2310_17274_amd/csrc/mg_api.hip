@@ -552,13 +552,8 @@ bool serial_poses(const mg_batch* b, bool particles) {
 void wl_single(const mg_batch* b, int K, mg::WaveLinks& wl) {
   wl.one.S = 0;
   if (b->P != 1) return;
-  const mg_ctx* c = b->ctx;
-  const int w = b->world[0];
-  const bool set = w + 1 < (int)c->world_off.size();
   wl.one.S = b->seeds[0];
   wl.one.T = b->horizon[0];
-  wl.one.box_lo = set ? c->world_off[w] : 0;
-  wl.one.box_hi = set ? c->world_off[w + 1] : 0;
   wl.one.n_e = b->seeds[0] * b->horizon[0] * K;
 }
 
@@ -1745,7 +1740,6 @@ mg_status solve_fused(mg_ctx* c, mg_batch* b, const float* q_start, const float*
     key_push(key, c->d_box); key_push(key, c->d_world_off); key_push(key, b->slices);
     key_push(key, b->layout); key_push(key, b->wl_slices); key_push(key, c->n_self);
     key_push(key, b->wl_halves); key_push(key, b->wl_groups);
-    for (int v : c->world_off) key_push(key, v);
     for (int k = 0; k < K; ++k) key_push(key, alpha[k]);
     if (!b->gexec || key != b->gkey) {
       if (b->gexec) { (void)hipGraphExecDestroy(b->gexec); b->gexec = nullptr; }
@@ -1826,8 +1820,6 @@ mg_status mg_solve(mg_ctx* c, mg_batch* b, const float* q_start, const float* go
     key_push(key, b->layout); key_push(key, b->wl_slices); key_push(key, c->n_self);
     key_push(key, b->wl_halves);
     key_push(key, b->wl_groups);
-    // (one-problem launches carry the world's cuboid range by value)
-    for (int v : c->world_off) key_push(key, v);
     for (int k = 0; k < K; ++k) key_push(key, alpha[k]);
     if (!b->gexec || key != b->gkey) {
       if (b->gexec) { (void)hipGraphExecDestroy(b->gexec); b->gexec = nullptr; }

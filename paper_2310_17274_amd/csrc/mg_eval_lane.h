@@ -366,7 +366,8 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
   }
   int S, T, row0, seed0, w0, w1;
   if (a.wl.one.S > 0) {
-    S = a.wl.one.S; T = a.wl.one.T; row0 = 0; seed0 = 0; w0 = a.wl.one.box_lo; w1 = a.wl.one.box_hi;
+    const v4i pr = ((cv4i*)(a.prob))[1];
+    S = a.wl.one.S; T = a.wl.one.T; row0 = 0; seed0 = 0; w0 = pr.y; w1 = pr.z;
   } else {
     cv4i* pr = (cv4i*)(a.prob + p);
     const v4i p0 = pr[0], p1 = pr[1];

@@ -370,12 +370,13 @@ __device__ __forceinline__ void eval_wl_body(const EvalArgs& a, const FA& fa) {
   // ---- everything is read from memory in two dependent rounds: the
   //      chunk's record and this wave's tables (scalar loads), then the
   //      workgroup's staging into LDS; after that only LDS is read ----
-  // (one problem: the record follows from the workgroup index, one memory
-  // round fewer)
+  // (one problem: the record follows from the workgroup index but for the
+  // cuboid range, one memory round fewer for everything else)
   v4i c0, c1;
   if (a.wl.one.S > 0) {
+    const v4i pr = ((cv4i*)(a.prob))[1];
     c0 = v4i{0, bx * E, a.wl.one.S, a.wl.one.T};
-    c1 = v4i{a.wl.one.box_lo, a.wl.one.box_hi, 0, a.wl.one.n_e};
+    c1 = v4i{pr.y, pr.z, 0, a.wl.one.n_e};
   } else {
     c0 = ((cv4i*)(a.wl.chunk + bx))[0];
     c1 = ((cv4i*)(a.wl.chunk + bx))[1];

@@ -92,10 +92,12 @@ struct WlChunk {
 // effector) for all 64, the last wave owns the joint terms.
 struct WaveLinks {
   const WlChunk* chunk;    // [workgroups along x] (per candidate count K)
-  // one problem (one.S > 0): chunk x is {0, x E, one.S, one.T, one.box_lo,
-  // one.box_hi, 0, one.n_e}, formed without reading the table
+  // one problem (one.S > 0): chunk x is {0, x E, one.S, one.T, the problem's
+  // box_lo, box_hi, 0, one.n_e}, formed without reading the table.  (What a batch
+  // keeps for life goes by value; the cuboid range is read from the problem's
+  // record, which mg_set_worlds rewrites under launches already captured.)
   struct {
-    int S, T, box_lo, box_hi, n_e;
+    int S, T, n_e;
   } one;
   const int4* info;        // [L]: chain depth, spheres, end effector or -1, 0
   const int* joint_rec;    // [D][2]: chain position of joint j (its link's depth - 1) and
