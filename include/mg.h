@@ -277,7 +277,9 @@ mg_status mg_ee_pose(mg_ctx *ctx, int rows, const float *q, float *pose, void *s
  * Autotuner for a batch's launch shape: times the line-search evaluation
  * kernel for K candidates under every layout and slice count the library
  * offers for this robot (mg_time_eval with `launches` launches each) and
- * fixes the fastest for every later call on this batch.  *slices_out (may
+ * fixes the fastest for every later launch of that many evaluations (rows
+ * times candidates) on this batch; launches of another number take the
+ * library's default, until mg_batch_set_layout replaces the choice.  *slices_out (may
  * be NULL) receives the slice count for the lane-per-link layout, minus
  * the workgroups per 64 evaluations for the wave-per-link layout, -8 for
  * two waves per link, -16 for two slot groups per wave or -32 for four.

@@ -153,7 +153,8 @@ struct mg_batch {
   std::vector<hipEvent_t> ev_start, ev_stop;
   int ev_next = 0, ev_count = 0;
   int slices = -1;    // cuboid slices index (-1: automatic)
-  long tuned_evals = 0;   // evaluations of the launch the autotuner chose `slices` for
+  bool slices_set = false;   // it came from mg_batch_set_layout: holds for every launch
+  long tuned_evals = 0;   // evaluations of the launch the autotuner chose layout and slices for (0: not tuned)
   int layout = -1;    // evaluation layout: -1 automatic, 0 lane per link, 1 wave per link
   bool layout_set = false;   // the layout came from mg_batch_set_layout (not the autotuner)
   // wave-per-link chunks of 64 evaluations, per candidate count K
@@ -492,11 +493,12 @@ mg_status check_params(const mg_params* p) {
 // (us per launch with one copy and two, 7 joints: 8192 evaluations 11.5 / 10.9
 // in a sparse world, 17.6 / 14.5 in a dense one; 12288 12.8 / 12.6 and 18.0 /
 // 16.6; 16384 12.2 / 14.6 and 19.3 / 19.4; two arms, swept: 6144 149 / 111,
-// 12288 176 / 202).  MG_CUBOID_SLICES forces a choice; one of the autotuner
-// holds for the number of evaluations it timed.
+// 12288 176 / 202).  MG_CUBOID_SLICES forces a choice, before it one of
+// mg_batch_set_layout; one of the autotuner holds for the number of
+// evaluations it timed.
 int pick_slices(const mg_batch* b, long n_evals) {
   const int n_opts = b->ctx->lpe == 8 ? kNumSlices : kNumSlices - 1;
-  if (b->slices >= 0 && (b->layout_set || n_evals == b->tuned_evals)) return b->slices;
+  if (b->slices >= 0 && (b->slices_set || n_evals == b->tuned_evals)) return b->slices;
   const char* env = getenv("MG_CUBOID_SLICES");
   if (env) {
     const int h = atoi(env);
@@ -1361,7 +1363,7 @@ mg_status mg_autotune(mg_ctx* c, mg_batch* b, const float* q_start, const float*
   if (opts.empty()) return fail(MG_ERR_UNSUPPORTED, "no evaluation layout fits this robot");
   size_t best = 0;
   float best_us = 3.0e38f;
-  b->layout_set = false;
+  b->layout_set = b->slices_set = false;
   b->tuned_evals = (long)b->rows * K;
   for (size_t o = 0; o < opts.size(); ++o) {
     b->layout = opts[o].layout;
@@ -1375,6 +1377,7 @@ mg_status mg_autotune(mg_ctx* c, mg_batch* b, const float* q_start, const float*
         (st = mg_time_eval(c, b, q_start, goal, x, dir, K, alpha, launches, &us, stream)) != MG_OK) {
       b->slices = -1;
       b->layout = -1;
+      b->tuned_evals = 0;
       b->wl_slices = 0;
       b->wl_halves = 0;
       b->wl_groups = 1;
@@ -1463,18 +1466,10 @@ mg_status mg_batch_set_layout(mg_batch* b, int layout, int slices) {
     return fail(MG_ERR_UNSUPPORTED, "two slot groups per wave need no self-collision and 4 or more slots per link");
   if (layout == 4 && !wl_groups_possible(b->ctx, 4))
     return fail(MG_ERR_UNSUPPORTED, "four slot groups per wave need no self-collision and 8 or more slots per link");
-  b->wl_halves = layout == 2 ? 2 : (layout == 1 || layout >= 3 ? 1 : 0);
-  b->wl_groups = layout == 4 ? 4 : layout == 3 ? 2 : 1;
-  b->layout_set = layout >= 0;
+  int hi = -1;
   if (layout >= 2) {
     if (slices > 1) return fail(MG_ERR_ARG, "layouts 2, 3 and 4 take one workgroup per chunk of evaluations");
-    b->layout = 1;
-    b->slices = -1;
-    b->wl_slices = 1;
-    return MG_OK;
-  }
-  int hi = -1;
-  if (slices != 0) {
+  } else if (slices != 0) {
     for (int i = 0; i < kNumSlices; ++i)
       if (kSlices[i] == slices && slices <= 4) hi = i;
     // (wave per link also takes 8 and 16 workgroups per chunk)
@@ -1483,9 +1478,15 @@ mg_status mg_batch_set_layout(mg_batch* b, int layout, int slices) {
     if (layout == 1 && slices > b->wl_slices_max)
       return fail(MG_ERR_SHAPE, "this batch holds at most %d wave-per-link slices", b->wl_slices_max);
   }
-  b->layout = layout;
-  b->slices = layout == 1 ? -1 : hi;
-  b->wl_slices = layout == 1 ? slices : 0;
+  // (a refused call has changed nothing)
+  b->layout_set = layout >= 0;
+  b->layout = std::min(layout, 1);
+  b->wl_halves = layout == 2 ? 2 : (layout == 1 || layout >= 3 ? 1 : 0);
+  b->wl_groups = layout == 4 ? 4 : layout == 3 ? 2 : 1;
+  b->wl_slices = layout >= 2 ? 1 : layout == 1 ? slices : 0;
+  b->slices = layout >= 1 ? -1 : hi;
+  b->slices_set = b->slices >= 0;
+  b->tuned_evals = 0;
   return MG_OK;
 }
 

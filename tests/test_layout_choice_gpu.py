@@ -1,0 +1,58 @@
+"""What decides on a batch's launch shape: mg_batch_set_layout, the autotuner,
+the library's default, in any order."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2310_17274_amd import _lib
+from paper_2310_17274_amd import workloads as wl
+from tests.test_parity_gpu import Case
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(seeds=3, horizon=7, n_box=130, **kw):
+    """A world crowded enough that every number of copies sums in an order of
+    its own."""
+    robot = wl.make_arm(seed=0, n_spheres=52)
+    return Case(robot, wl.make_worlds(21, [n_box]), wl.make_batch(robot, 22, [seeds], [horizon], [0], noise=0.1), **kw)
+
+
+def _eval(case, K=4):
+    o = case.ctx.mg_linesearch_eval(case.b, case.q_start, case.goal, case.x, torch.full_like(case.x, 0.05),
+                                    [float(a) for a in np.linspace(0.05, 1.0, K)])
+    torch.cuda.synchronize()
+    return [t.cpu().numpy() for t in o]
+
+
+def _same(a, b):
+    return all(np.array_equal(x, y) for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("tuned", [False, True])
+@pytest.mark.parametrize("swept", [0, 1])
+def test_slices_of_the_default_layout(swept, tuned):
+    """Layout -1 with a slice count is lane per link with that many copies,
+    before and after an autotuning."""
+    case = _case(params=dict(swept=swept))
+    seen = []
+    for slices in (1, 2, 4):
+        if tuned:
+            case.ctx.mg_autotune(case.b, case.q_start, case.goal, case.x, torch.zeros_like(case.x), [0.5, 1.0],
+                                 launches=1)
+        case.b.mg_batch_set_layout(-1, slices)
+        got = _eval(case)
+        case.b.mg_batch_set_layout(0, slices)
+        assert _same(got, _eval(case))
+        seen.append(got)
+    assert not _same(seen[0], seen[1]) and not _same(seen[1], seen[2])
+
+
+def test_refused_layout_changes_nothing():
+    case = _case()
+    case.b.mg_batch_set_layout(-1, 2)
+    want = _eval(case)
+    for bad in ((3, 2), (0, 8), (1, 5), (5, 0)):
+        with pytest.raises(_lib.MgError):
+            case.b.mg_batch_set_layout(*bad)
+        assert _same(_eval(case), want)
