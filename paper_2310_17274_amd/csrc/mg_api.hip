@@ -658,8 +658,6 @@ mg_status common_checks(mg_ctx* c, mg_batch* b) {
   return MG_OK;
 }
 
-// Launch an evaluation in the batch's layout: lane per link (cuboid slices
-// index hi) or wave per link.
 // Wave-per-link slices: the forced count, else enough workgroups for two
 // per CU.
 int wl_slices(const mg_batch* b, int K) {
@@ -669,24 +667,46 @@ int wl_slices(const mg_batch* b, int K) {
   return h;
 }
 
+// The shape of a batch's evaluation launch with K candidates: everything
+// that the caller, the autotuner or the library's rules choose.
+struct Shape {
+  int wl;                // wave per link, else lane per link
+  int hi, serial;        // lane per link: copies (index), poses link by link
+  int halves, groups, slices;   // wave per link
+};
+Shape shape_of(const mg_batch* b, int K) {
+  Shape sh{};
+  sh.wl = use_wl(b, K);
+  if (!sh.wl) {
+    sh.hi = pick_slices(b, (long)b->rows * K);
+    sh.serial = serial_poses(b, false);
+    return sh;
+  }
+  // two slot groups per wave when chosen; else two waves per link where
+  // they fit (shorter waves), unless forced
+  sh.groups = b->wl_groups > 1 && wl_groups_possible(b->ctx, b->wl_groups) ? b->wl_groups : 1;
+  sh.halves = sh.groups > 1 ? 1 : (b->wl_halves > 0 ? b->wl_halves : (wl_halves_possible(b->ctx) ? 2 : 1));
+  sh.slices = sh.halves == 2 || sh.groups > 1 ? 1 : wl_slices(b, K);
+  return sh;
+}
+
+// Launch an evaluation in the batch's layout: lane per link (copies index
+// hi) or wave per link.
 // slices_ok = false keeps the wave-per-link layout at one workgroup per
 // chunk (no slice scratch or arrival counters of the batch).
 hipError_t launch_layout(mg_batch* b, mg::EvalArgs a, int hi, bool cand, bool grad, hipStream_t s,
                          bool slices_ok = true, const mg::SelFuse* fs = nullptr) {
-  if (use_wl(b, a.K)) {
+  const Shape sh = shape_of(b, a.K);
+  if (sh.wl) {
     a.wl.part = b->wl_part;
     a.wl.count = b->wl_count;
-    // two slot groups per wave when chosen; else two waves per link where
-    // they fit (shorter waves), unless forced
-    const int groups = b->wl_groups > 1 && wl_groups_possible(b->ctx, b->wl_groups) ? b->wl_groups : 1;
-    const int halves = groups > 1 ? 1 : (b->wl_halves > 0 ? b->wl_halves : (wl_halves_possible(b->ctx) ? 2 : 1));
-    if (halves == 2 && !wl_halves_possible(b->ctx)) return hipErrorInvalidValue;
-    a.wl.halves = halves;
-    a.wl.groups = groups;
-    a.wl.chunk = b->d_chunk_wl[a.K][groups_index(groups)];
+    if (sh.halves == 2 && !wl_halves_possible(b->ctx)) return hipErrorInvalidValue;
+    a.wl.halves = sh.halves;
+    a.wl.groups = sh.groups;
+    a.wl.chunk = b->d_chunk_wl[a.K][groups_index(sh.groups)];
     // (the speed's gradient terms need every cuboid of a sphere in one workgroup)
-    const int wls = (halves == 2 || groups > 1 || !slices_ok || (a.sp_h && grad)) ? 1 : wl_slices(b, a.K);
-    return mg::launch_eval_wl(a, b->chunks_wl[a.K][groups_index(groups)], wls, cand, grad, s, fs);
+    const int wls = !slices_ok || (a.sp_h && grad) ? 1 : sh.slices;
+    return mg::launch_eval_wl(a, b->chunks_wl[a.K][groups_index(sh.groups)], wls, cand, grad, s, fs);
   }
   if (fs) return hipErrorInvalidValue;
   return mg::launch_eval(a, lane_blocks(b, hi, a.K, a), cand, grad, s);
@@ -1738,9 +1758,7 @@ mg_status solve_fused(mg_ctx* c, mg_batch* b, const float* q_start, const float*
     std::vector<char> key;
     key_push(key, 1); key_push(key, q_start); key_push(key, goal); key_push(key, x); key_push(key, m);
     key_push(key, K); key_push(key, mode); key_push(key, gi); key_push(key, c->params);
-    key_push(key, c->d_box); key_push(key, c->d_world_off); key_push(key, b->slices);
-    key_push(key, b->layout); key_push(key, b->wl_slices); key_push(key, c->n_self);
-    key_push(key, b->wl_halves); key_push(key, b->wl_groups);
+    key_push(key, c->d_box); key_push(key, c->n_self); key_push(key, shape_of(b, K));
     for (int k = 0; k < K; ++k) key_push(key, alpha[k]);
     if (!b->gexec || key != b->gkey) {
       if (b->gexec) { (void)hipGraphExecDestroy(b->gexec); b->gexec = nullptr; }
@@ -1817,10 +1835,7 @@ mg_status mg_solve(mg_ctx* c, mg_batch* b, const float* q_start, const float* go
     key_push(key, 0);
     key_push(key, q_start); key_push(key, goal); key_push(key, x); key_push(key, m); key_push(key, K);
     key_push(key, mode); key_push(key, graph_inner); key_push(key, c->params);
-    key_push(key, c->d_box); key_push(key, c->d_world_off); key_push(key, b->slices);
-    key_push(key, b->layout); key_push(key, b->wl_slices); key_push(key, c->n_self);
-    key_push(key, b->wl_halves);
-    key_push(key, b->wl_groups);
+    key_push(key, c->d_box); key_push(key, c->n_self); key_push(key, shape_of(b, K));
     for (int k = 0; k < K; ++k) key_push(key, alpha[k]);
     if (!b->gexec || key != b->gkey) {
       if (b->gexec) { (void)hipGraphExecDestroy(b->gexec); b->gexec = nullptr; }

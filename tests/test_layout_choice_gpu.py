@@ -1,5 +1,7 @@
 """What decides on a batch's launch shape: mg_batch_set_layout, the autotuner,
 the library's default, in any order."""
+import os
+
 import numpy as np
 import pytest
 import torch
@@ -56,3 +58,47 @@ def test_refused_layout_changes_nothing():
         with pytest.raises(_lib.MgError):
             case.b.mg_batch_set_layout(*bad)
         assert _same(_eval(case), want)
+
+
+def _solve(case, K, x, use_graph):
+    """Six iterations, or two replays of a graph of three."""
+    x.copy_(case.x)
+    o = case.ctx.mg_solve(case.b, case.q_start, case.goal, x, 6, 4, [float(a) for a in np.linspace(0.1, 1.0, K)],
+                          graph_inner=3, use_graph=use_graph)
+    torch.cuda.synchronize()
+    return [t.cpu().numpy().copy() for t in o]
+
+
+def test_solve_graph_is_that_of_the_shape_asked_for():
+    """A graph captured under one launch shape is not replayed under another:
+    copies by the library's rule, by the environment, by the autotuner's choice
+    for another number of candidates, by the caller."""
+    case = _case(horizon=9)
+    x = torch.empty_like(case.x)                          # (one buffer: the graph's key holds its address)
+    seen = []
+
+    def check():
+        got = _solve(case, 4, x, True)
+        assert _same(got, _solve(case, 4, x, False))
+        seen.append(got)
+
+    check()
+    old = os.environ.get("MG_CUBOID_SLICES")
+    try:
+        for n in ("1", "2", "4"):
+            os.environ["MG_CUBOID_SLICES"] = n
+            check()
+    finally:
+        os.environ.pop("MG_CUBOID_SLICES")
+        if old is not None:
+            os.environ["MG_CUBOID_SLICES"] = old
+    check()
+    assert not _same(seen[1], seen[2]) and not _same(seen[2], seen[3]) and _same(seen[0], seen[4])
+    choice = case.ctx.mg_autotune(case.b, case.q_start, case.goal, case.x, torch.zeros_like(case.x), [0.5, 1.0],
+                                  launches=2)
+    check()                                               # (not the count that was tuned)
+    case.b.mg_batch_set_layout(*((0, choice) if choice in (1, 2, 4) else (1, 1)))
+    check()
+    for layout in ((-1, 1), (0, 4), (-1, 0), (1, 1), (1, 2), (3, 0), (2, 0)):
+        case.b.mg_batch_set_layout(*layout)
+        check()
