@@ -186,7 +186,7 @@ __device__ __forceinline__ void evals_min(float* v, int GE) {
   }
 }
 // Stores and loads that meet between workgroups of one launch (the XCDs' L2
-// caches are not coherent).
+// caches are not coherent): through to memory, past the caches.
 __device__ __forceinline__ void st_agent(float* p, float v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -916,8 +916,25 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const EvalArgs a) {
   // ---- the seeds' sums: every workgroup adds its rows to its seeds' counts,
   //      and the one that completes a seed sums the rows, a wave per
   //      candidate, in the order of reduce_kernel (same bits) ----
+  // What makes a row's three values visible to the workgroup that sums them,
+  // wherever it runs:
+  //   1. they are stored and loaded by agent-scope atomics (sc1 set: the store
+  //      goes through this XCD's L2 to memory, the load is not served from a
+  //      line that the reader's L2 or L1 kept), so no cache holds an older or a
+  //      newer value of them, and none has to be written back or invalidated;
+  //   2. every wave waits here until its stores are acknowledged (vmcnt 0), and
+  //      the barrier makes all of the workgroup's waves have done so before its
+  //      count is raised by an agent-scope atomic;
+  //   3. the count reaches T only after every workgroup's addition, the adding
+  //      wave waits for the value that its addition returns, and its workgroup
+  //      loads the rows behind the barrier after that.
+  // That is the order which a release and an acquire on the count would ask for,
+  // without what those do besides: they write back and invalidate the whole
+  // L2, gradients and all, once per workgroup (us per call so, and with
+  // __ATOMIC_ACQ_REL: 32 x 32, K = 8 15.5 / 21.1; 256 x 32 13.5 / 18.6; 768 x 32
+  // 19.6 / 25.8; 4 x 32 12.4 both).
   if (a.sum.count) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's rows are where every XCD sees them
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (2)
     __syncthreads();
     int* s_done = reinterpret_cast<int*>(s_mem);
     const int sa = first / T, ns = (min(first + RB, nrows) - 1) / T - sa + 1;
