@@ -724,6 +724,20 @@ mg::ReduceArgs reduce_args(const mg_batch* b, int K, float* cost, float* min_cle
                         b->cost_e, b->mc_e, gd ? b->gd_e : nullptr, cost, min_clear, gd};
 }
 
+// Whether an output (its floats from a pointer on) lies over an input of the
+// evaluation: the launch cannot write it then while other workgroups still
+// read, and the outputs go through the batch's workspace.
+bool over_inputs(const mg_batch* b, const float* q_start, const float* goal, const float* x, const float* d,
+                 std::initializer_list<std::pair<const float*, size_t>> outs) {
+  const size_t RD = (size_t)b->rows * b->ctx->D;
+  const std::pair<const float*, size_t> ins[] = {{q_start, (size_t)b->P * b->ctx->D},
+                                                 {goal, (size_t)b->P * b->ctx->n_ee * 7}, {x, RD}, {d, RD}};
+  for (const auto& o : outs)
+    for (const auto& i : ins)
+      if (o.first && i.first && o.first < i.first + i.second && i.first < o.first + o.second) return true;
+  return false;
+}
+
 mg_status enqueue_eval(mg_ctx* c, mg_batch* b, const float* q_start, const float* goal,
                        const float* x, const float* d, int K, const float* alpha, bool grad,
                        float* grad_out, float* pe_out, hipStream_t s, const EvalOut* eo = nullptr,
@@ -1291,7 +1305,13 @@ mg_status mg_cost_grad(mg_ctx* c, mg_batch* b, const float* q_start, const float
   if (!q_start || !goal || !q || !cost) return fail(MG_ERR_ARG, "null q_start, goal, q or cost");
   hipStream_t s = static_cast<hipStream_t>(stream);
   const mg::SeedSums sums{cost, min_clear, nullptr, nullptr, 0};
-  return enqueue_eval(c, b, q_start, goal, q, nullptr, 1, nullptr, grad != nullptr, grad, nullptr, s, nullptr, &sums);
+  const size_t n = b->n_seeds;
+  if (!over_inputs(b, q_start, goal, q, nullptr, {{cost, n}, {min_clear, n}}))
+    return enqueue_eval(c, b, q_start, goal, q, nullptr, 1, nullptr, grad != nullptr, grad, nullptr, s, nullptr, &sums);
+  if ((st = enqueue_eval(c, b, q_start, goal, q, nullptr, 1, nullptr, grad != nullptr, grad, nullptr, s)) != MG_OK)
+    return st;
+  HIP_TRY(mg::launch_reduce(reduce_args(b, 1, cost, min_clear, nullptr), s));
+  return MG_OK;
 }
 
 mg_status mg_lbfgs_step(mg_ctx* c, mg_batch* b, int m, int reset, const float* x, const float* g,
@@ -1329,7 +1349,13 @@ mg_status mg_linesearch_eval(mg_ctx* c, mg_batch* b, const float* q_start, const
   // the launch mg_linesearch and mg_solve make for these K candidates, its
   // gradients straight into the caller's array
   const mg::SeedSums sums{cost, min_clear, gd, nullptr, 0};
-  return enqueue_eval(c, b, q_start, goal, x, dir, K, alpha, true, grad, nullptr, s, nullptr, &sums);
+  const size_t n = (size_t)K * b->n_seeds, g = (size_t)K * b->rows * c->D;
+  if (!over_inputs(b, q_start, goal, x, dir, {{cost, n}, {min_clear, n}, {gd, n}, {grad, g}}))
+    return enqueue_eval(c, b, q_start, goal, x, dir, K, alpha, true, grad, nullptr, s, nullptr, &sums);
+  if ((st = enqueue_eval(c, b, q_start, goal, x, dir, K, alpha, true, nullptr, nullptr, s)) != MG_OK) return st;
+  HIP_TRY(mg::launch_reduce(reduce_args(b, K, cost, min_clear, gd), s));
+  if (grad) HIP_TRY(mg::launch_copy2(b->grad_e, grad, g, nullptr, nullptr, 0, s));
+  return MG_OK;
 }
 
 mg_status mg_linesearch_noalloc(mg_ctx* c, mg_batch* b, const float* q_start, const float* goal,
