@@ -280,7 +280,8 @@ mg_status mg_ee_pose(mg_ctx *ctx, int rows, const float *q, float *pose, void *s
  * fixes the fastest for every later launch of that many evaluations (rows
  * times candidates) on this batch; launches of another number take the
  * library's default, until mg_batch_set_layout replaces the choice.  *slices_out (may
- * be NULL) receives the slice count for the lane-per-link layout, minus
+ * be NULL) receives the slice count for the lane-per-link layout (8 too,
+ * which small batches take by default), minus
  * the workgroups per 64 evaluations for the wave-per-link layout, -8 for
  * two waves per link, -16 for two slot groups per wave or -32 for four.
  * Overwrites the batch's evaluation workspaces; not capturable. */

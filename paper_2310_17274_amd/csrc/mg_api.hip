@@ -496,9 +496,8 @@ mg_status check_params(const mg_params* p) {
 // 12288 176 / 202).  MG_CUBOID_SLICES forces a choice, before it one of
 // mg_batch_set_layout; one of the autotuner holds for the number of
 // evaluations it timed.
-int pick_slices(const mg_batch* b, long n_evals) {
+int default_slices(const mg_batch* b, long n_evals) {
   const int n_opts = b->ctx->lpe == 8 ? kNumSlices : kNumSlices - 1;
-  if (b->slices >= 0 && (b->slices_set || n_evals == b->tuned_evals)) return b->slices;
   const char* env = getenv("MG_CUBOID_SLICES");
   if (env) {
     const int h = atoi(env);
@@ -510,6 +509,10 @@ int pick_slices(const mg_batch* b, long n_evals) {
   for (int i = 0; i < n_opts; ++i)
     if (waves1 * kSlices[i] >= (i == 0 ? 2 * simds : simds)) return i;
   return n_opts - 1;
+}
+int pick_slices(const mg_batch* b, long n_evals) {
+  if (b->slices >= 0 && (b->slices_set || n_evals == b->tuned_evals)) return b->slices;
+  return default_slices(b, n_evals);
 }
 
 // Lane-per-link workgroup of a launch with K candidates per row: as many
@@ -1393,14 +1396,15 @@ mg_status mg_autotune(mg_ctx* c, mg_batch* b, const float* q_start, const float*
   if ((st = check_K_alpha(b, K, alpha)) != MG_OK) return st;
   if (!q_start || !goal || !x || !dir) return fail(MG_ERR_ARG, "null argument");
   if (launches < 1) return fail(MG_ERR_ARG, "launches must be >= 1");
-  // candidates: lane per link with 1, 2 or 4 cuboid slices per workgroup;
-  // wave per link with two waves per link; wave per link with 1, 2 or 4
-  // workgroups per 64 evaluations.  Each is {layout, slices index, halves,
-  // workgroup slices}.
+  // candidates: lane per link with 1, 2 or 4 copies, and with 8 where that is
+  // what an untuned launch would take; wave per link with two waves per link;
+  // wave per link with 1, 2 or 4 workgroups per 64 evaluations.  Each is
+  // {layout, slices index, halves, workgroup slices}.
   struct Opt { int layout, hi, halves, wls, groups; };
   std::vector<Opt> opts;
   if (!needs_wl(c))
-    for (int hi = 0; hi < 3; ++hi) opts.push_back({0, hi, 0, 0, 1});
+    for (int hi = 0; hi < 3 || (hi == 3 && default_slices(b, (long)b->rows * K) == 3); ++hi)
+      opts.push_back({0, hi, 0, 0, 1});
   if (wl_groups_possible(c, 4)) opts.push_back({1, -1, 1, 1, 4});
   if (wl_groups_possible(c)) opts.push_back({1, -1, 1, 1, 2});
   if (wl_halves_possible(c)) opts.push_back({1, -1, 2, 1, 1});

@@ -102,3 +102,19 @@ def test_solve_graph_is_that_of_the_shape_asked_for():
     for layout in ((-1, 1), (0, 4), (-1, 0), (1, 1), (1, 2), (3, 0), (2, 0)):
         case.b.mg_batch_set_layout(*layout)
         check()
+
+
+def test_autotuner_times_the_default_shape():
+    """A batch so small that its default is eight copies: tuned, it is the
+    default's bits or another option's, never a slower shape for want of having
+    timed the default (its choice is one of the numbers that the header lists)."""
+    case = _case(seeds=2, horizon=3, n_box=20)
+    want = _eval(case, K=2)
+    choice = case.ctx.mg_autotune(case.b, case.q_start, case.goal, case.x, torch.zeros_like(case.x), [0.5, 1.0],
+                                  launches=3)
+    assert choice in (1, 2, 4, 8, -1, -2, -4, -8, -16, -32)
+    got = _eval(case, K=2)
+    for a, b in zip(got, want):
+        assert np.allclose(a, b, rtol=1e-5, atol=1e-5 * np.abs(b).max())
+    if choice == 8:
+        assert _same(got, want)
