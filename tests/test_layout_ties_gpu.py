@@ -2,6 +2,8 @@
 cuboid with two faces equally near, where the gradient is one face's normal or
 the other's.  A batch whose layout the autotuner chooses decides them as the
 wave-per-link layout does, whichever layout runs."""
+import os
+
 import numpy as np
 import pytest
 import torch
@@ -91,3 +93,22 @@ def test_swept_particles_cost_as_wave_per_link(arms):
         torch.cuda.synchronize()
         costs.append((o[-1] if isinstance(o, (tuple, list)) else o).cpu().numpy().astype(np.float64))
     assert np.allclose(costs[0], costs[1], rtol=1e-5, atol=0.0)
+
+
+@pytest.mark.parametrize("copies", [1, 2, 4])
+def test_two_arms_trace_alike_with_every_number_of_copies(copies):
+    """The trace queue over five tiles of cuboids (an untuned number of
+    candidates on a tuned batch)."""
+    case = _tie_case(wl.make_two_arm(seed=0, n_spheres=120), 24, 6, 300, 1)
+    case.b.mg_batch_set_layout(1, 1)
+    want = _grads(case, 4)
+    case.ctx.mg_autotune(case.b, case.q_start, case.goal, case.x, torch.zeros_like(case.x), [0.5, 0.5], launches=1)
+    old = os.environ.get("MG_CUBOID_SLICES")
+    os.environ["MG_CUBOID_SLICES"] = str(copies)
+    try:
+        got = _grads(case, 4)
+    finally:
+        os.environ.pop("MG_CUBOID_SLICES")
+        if old is not None:
+            os.environ["MG_CUBOID_SLICES"] = old
+    assert np.abs(got - want).max() < TOL
