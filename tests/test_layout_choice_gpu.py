@@ -118,3 +118,22 @@ def test_autotuner_times_the_default_shape():
         assert np.allclose(a, b, rtol=1e-5, atol=1e-5 * np.abs(b).max())
     if choice == 8:
         assert _same(got, want)
+
+
+@pytest.mark.parametrize("seeds,K", [(8, 8), (64, 8), (65, 8), (128, 4), (129, 4), (256, 8)])
+def test_tuned_batches_fold_up_to_one_workgroup_a_cu(seeds, K):
+    """With self-collision the tuner has wave per link alone to choose from (one
+    slot group): such a batch folds its choices up to 256 workgroups of 64
+    evaluations, a layout fixed by the caller at every size, two waves per
+    link never."""
+    robot = wl.make_arm(seed=0, n_spheres=52)
+    case = Case(robot, wl.make_worlds(8, [4]), wl.make_batch(robot, 77, [seeds], [32], [0]),
+                self_pairs=wl.self_pairs(robot))
+    alpha = [float(a) for a in np.linspace(0.1, 1.0, K)]
+    choice = case.ctx.mg_autotune(case.b, case.q_start, case.goal, case.x, torch.zeros_like(case.x), alpha, launches=1)
+    assert choice < 0
+    assert bool(case.ctx.mg_solve_fuses(case.b, K, 4, case.x)) == (choice != -8 and seeds * 32 * K // 64 <= 256)
+    case.b.mg_batch_set_layout(1, 1)
+    assert case.ctx.mg_solve_fuses(case.b, K, 4, case.x)
+    case.b.mg_batch_set_layout(2, 0)
+    assert not case.ctx.mg_solve_fuses(case.b, K, 4, case.x)
