@@ -119,7 +119,9 @@ mg_status mg_set_params(mg_ctx *ctx, const mg_params *params);
  * pose: DEVICE [n][7] box-to-world poses; dims: DEVICE [n][3] full side
  * lengths (> 0).  The cuboids are converted on stream into the library's own
  * layout; pose/dims may be reused by the caller once the stream reaches this
- * point.  Reallocates (not capturable) only when n or n_worlds grow. */
+ * point.  Waits for the stream (not capturable).  Calls captured before follow
+ * the new worlds unless n has grown past every earlier one (then the cuboids
+ * are reallocated and the calls have to be captured again). */
 mg_status mg_set_worlds(mg_ctx *ctx, int n_worlds, const int *offsets,
                         const float *pose, const float *dims, void *stream);
 

@@ -110,8 +110,7 @@ struct mg_ctx {
   int4* d_self_pairs = nullptr;
   Box* d_box = nullptr;
   int box_cap = 0, n_boxes = 0;
-  int* d_world_off = nullptr;
-  int world_cap = 0, n_worlds = 0;
+  int n_worlds = 0;
   size_t lds_max = 64 * 1024;    // LDS one workgroup may hold on this device
   std::vector<int> world_off;    // host copy of the cuboid offsets
   std::vector<mg_batch*> batches;   // live batches (their chunk records name cuboid ranges)
@@ -654,7 +653,7 @@ mg_status wl_chunks_upload(mg_batch* b) {
 mg_status common_checks(mg_ctx* c, mg_batch* b) {
   if (!c || !b) return fail(MG_ERR_ARG, "null context or batch");
   if (b->ctx != c) return fail(MG_ERR_ARG, "batch belongs to another context");
-  if (!c->d_world_off || c->n_worlds <= 0) return fail(MG_ERR_STATE, "no world set (mg_set_worlds)");
+  if (c->n_worlds <= 0) return fail(MG_ERR_STATE, "no world set (mg_set_worlds)");
   for (int p = 0; p < b->P; ++p)
     if (b->world[p] >= c->n_worlds)
       return fail(MG_ERR_STATE, "problem %d uses world %d but only %d worlds are set", p, b->world[p], c->n_worlds);
@@ -1062,7 +1061,7 @@ void mg_destroy(mg_ctx* c) {
   dev_free(c->d_lane_info); dev_free(c->d_lane_sphere); dev_free(c->d_part_sphere);
   dev_free(c->d_wl_info); dev_free(c->d_wl_chain); dev_free(c->d_wl_ball);
   dev_free(c->d_slot_sphere); dev_free(c->d_self_pairs); dev_free(c->d_chain_rec); dev_free(c->d_joint_rec);
-  dev_free(c->d_box); dev_free(c->d_world_off);
+  dev_free(c->d_box);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
   delete c;
 }
@@ -1096,15 +1095,9 @@ mg_status mg_set_worlds(mg_ctx* c, int n_worlds, const int* offsets, const float
     if ((st = dev_alloc(&c->d_box, n)) != MG_OK) return st;
     c->box_cap = n;
   }
-  if (n_worlds + 1 > c->world_cap) {
-    HIP_TRY(hipStreamSynchronize(s));
-    dev_free(c->d_world_off);
-    if ((st = dev_alloc(&c->d_world_off, n_worlds + 1)) != MG_OK) return st;
-    c->world_cap = n_worlds + 1;
-  }
-  // offsets are tiny host data; a synchronous copy keeps the host array free
+  // (what the stream still evaluates reads the old cuboids and their ranges,
+  // which the batches' records are given below by synchronous copies)
   HIP_TRY(hipStreamSynchronize(s));
-  HIP_TRY(hipMemcpy(c->d_world_off, offsets, (n_worlds + 1) * sizeof(int), hipMemcpyHostToDevice));
   HIP_TRY(mg::launch_boxes(pose, dims, n, c->d_box, s));
   c->n_boxes = n;
   c->n_worlds = n_worlds;
