@@ -7,6 +7,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import time
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB = os.path.join(HERE, "libmg.so")
@@ -49,8 +50,10 @@ def build(verbose: bool = False, jobs: int | None = None, incremental: bool = Fa
             print(" ".join(cmd), flush=True)
         log = open(obj + ".log", "w")
         procs.append((src, subprocess.Popen(cmd, stdout=log, stderr=subprocess.STDOUT), obj + ".log"))
+        # (the next starts as soon as any is done: the first source takes longer
+        # than all others together on the remaining cores)
         while sum(p.poll() is None for _, p, _ in procs) >= jobs:
-            procs[[p.poll() is None for _, p, _ in procs].index(True)][1].wait()
+            time.sleep(0.05)
     failed = False
     for src, p, log in procs:
         p.wait()
