@@ -119,7 +119,8 @@ __device__ __forceinline__ void link_pose_serial(const float4& f0, const float4&
 // the exact term is, 64 lanes waited for the few that step: 6144 rows of two
 // arms among 500 cuboids, K = 4, took 579 us, 440 with the queue.)  A wave
 // then holds neighbouring rows of one candidate and shares their poses, which
-// lets three workgroups into a CU's LDS instead of two (410 us, now 315).
+// lets three workgroups into a CU's LDS instead of two (410 us, now 315; over
+// other inputs of these sizes a launch takes 240 to 315).
 // The lanes' sums go back to the owners (evaluation, link) through an LDS
 // row per lane: each owner finds its rows from six ballots of the owners'
 // bits and adds them in lane order, so the results are deterministic.  (LDS
@@ -140,7 +141,7 @@ __device__ __forceinline__ void link_pose_serial(const float4& f0, const float4&
 //   the same without the sweep                                         180 / 298
 //   128 seeds x 32, 40 cuboids, K = 8                                  16.1 / 24.1
 //   32 seeds x 32, 40 cuboids, K = 8                                   11.1 / 11.6
-//   4 seeds x 32, 10 cuboids, K = 4                                    7.2 / 9.5
+//   4 seeds x 32, 10 cuboids, K = 4                                    7.6 / 9.4
 // Large batches are bound by the vector instructions issued (some 280 per
 // evaluation, half of them kinematics, joint and pose terms, at one per four
 // cycles and SIMD), small ones by one wave's chain of them.

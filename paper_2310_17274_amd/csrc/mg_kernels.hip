@@ -630,7 +630,7 @@ hipError_t launch_steer_points(const SteerArgs& a, hipStream_t s) {
 // ballot (its rank) and a shift by one lane.  (A list per lane met its bar
 // k (1 + ln(n / 64 k)) times in every lane, so that nearly every step of a
 // wave ran the insertion over KMAX registers.)  12000 x 12000 x 7, k = 11:
-// 672 us before, 157 now.  What bounds it is the arithmetic that the exact
+// 672 us before, 139 now.  What bounds it is the arithmetic that the exact
 // sums need, three operations per joint and node (77 us of that), and the
 // insertions.
 constexpr int kKnnTile = kBlock;
@@ -715,8 +715,8 @@ hipError_t launch_knn_d(const KnnArgs& a, hipStream_t s) {
   // One query per wave while all of them are in flight at once (8192 waves:
   // eight on each SIMD of 256 CUs); above that, two share every node that a
   // wave reads (12000 nodes, k = 11, 7 joints: 10000 queries 129 us one by
-  // one, 123 by pairs; 14 joints 201 and 176; 12000 queries of 7 joints 157
-  // by pairs, 176 by fours).
+  // one, 123 by pairs; 14 joints 201 and 176; 12000 queries of 7 joints,
+  // before the next tile was read ahead, 157 by pairs and 176 by fours).
   constexpr int W = kBlock / kWave;
   if (a.n_queries > 8192) knn_kernel<D, 2><<<(a.n_queries + 2 * W - 1) / (2 * W), kBlock, 0, s>>>(a);
   else knn_kernel<D, 1><<<(a.n_queries + W - 1) / W, kBlock, 0, s>>>(a);
