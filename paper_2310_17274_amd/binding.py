@@ -67,15 +67,16 @@ class Batch:
         self.rows = int((self.seeds * self.horizon).sum())
         assert self.n_seeds == _lib.lib().mg_batch_seeds(h)
         assert self.rows == _lib.lib().mg_batch_rows(h)
+        # the horizon when every problem has the same one, else 0
+        self.uniform_T = int(self.horizon[0]) if (self.horizon == self.horizon[0]).all() else 0
         self._seed_of_row = None
 
     @property
     def seed_of_row(self):
-        """Seed of every trajectory row, for the backward of MgCost: on the
-        device from its first use on (built on each call, it cost an upload and
-        a wait for the stream: 32 seeds x 32 points forward and backward 206
-        us, now 134; built with every batch, 0.25 ms for 33024 rows that
-        programs without autograd never use)."""
+        """Seed of every trajectory row, for the backward of MgCost over
+        problems of several horizons: on the device from its first use on
+        (built on each call, it cost an upload and a wait for the stream;
+        built with every batch, 0.25 ms for 33024 rows)."""
         t = self._seed_of_row
         if t is None:
             # (the copy from host memory has ended when as_tensor returns)
@@ -464,7 +465,10 @@ class MgCost(torch.autograd.Function):
         ctx, b, q_start, goal = fctx.mg
         _, g, _ = ctx.mg_cost_grad(b, q_start, goal, q.detach().contiguous(), grad=True,
                                    min_clear=False)
-        seed_of_row = b.seed_of_row.to(q.device)
-        seed_of_row.record_stream(torch.cuda.current_stream(q.device))   # (made on another call's stream)
-        scale = grad_out.index_select(0, seed_of_row)
+        if b.uniform_T:
+            scale = grad_out.unsqueeze(1).expand(-1, b.uniform_T).reshape(-1)
+        else:
+            seed_of_row = b.seed_of_row.to(q.device)
+            seed_of_row.record_stream(torch.cuda.current_stream(q.device))   # (made on another call's stream)
+            scale = grad_out.index_select(0, seed_of_row)
         return g * scale.view(-1, 1).to(g.dtype), None, None, None, None

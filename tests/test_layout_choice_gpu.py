@@ -8,7 +8,8 @@ import torch
 
 from paper_2310_17274_amd import _lib
 from paper_2310_17274_amd import workloads as wl
-from tests.test_parity_gpu import Case
+from tests.test_fullsize_gpu import _check_candidates, _direction, _oracle_candidates
+from tests.test_parity_gpu import Case, _dev
 
 pytestmark = pytest.mark.gpu
 
@@ -137,3 +138,22 @@ def test_tuned_batches_fold_up_to_one_workgroup_a_cu(seeds, K):
     assert case.ctx.mg_solve_fuses(case.b, K, 4, case.x)
     case.b.mg_batch_set_layout(2, 0)
     assert not case.ctx.mg_solve_fuses(case.b, K, 4, case.x)
+
+
+@pytest.mark.parametrize("horizon", [1, 2, 9])
+@pytest.mark.parametrize("arms", [1, 2])
+def test_tuned_traced_evaluation(arms, horizon):
+    """Poses formed link by link in the lane layout (a tuned batch that traces),
+    at a number of candidates that was tuned and at one that was not, against
+    the FP64 reference."""
+    robot = wl.make_arm(seed=0, n_spheres=23) if arms == 1 else wl.make_two_arm(seed=0, n_spheres=50)
+    case = Case(robot, wl.make_worlds(21, [12]), wl.make_batch(robot, 22, [5], [horizon], [0], noise=0.1),
+                params=dict(swept=1))
+    d = _direction(case, 0.1, 23)
+    case.ctx.mg_autotune(case.b, case.q_start, case.goal, case.x, _dev(d), [0.5, 1.0], launches=1)
+    for K in (2, 4):
+        alpha = [float(a) for a in np.linspace(0.05, 1.0, K)]
+        cost, gd, g, mc = (t.cpu().numpy() for t in case.ctx.mg_linesearch_eval(
+            case.b, case.q_start, case.goal, case.x, _dev(d), alpha))
+        ref_k = _oracle_candidates(case, case.batch.x0.reshape(-1, robot.dof), d, alpha)
+        _check_candidates(case, cost, gd, g, mc, ref_k, d)
